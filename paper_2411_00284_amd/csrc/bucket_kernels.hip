@@ -4,14 +4,14 @@
 // covers every parameter of a bucket.  The work of a launch is cut into tiles
 // that never cross a parameter (and, for the W-way copies, never cross one
 // rank's segment of a parameter), so that a tile is a plain contiguous copy,
-// cast or reduction with 16-byte vector accesses.  Tiles are numbered
-// parameter by parameter; the first tile of every parameter is kept in one
-// register per lane of a wavefront, and a ballot over it finds the parameter
-// of any tile in O(1).  The per-parameter table travels in the kernel
-// arguments: the pack and the reduce hold all of it in lanes (lane p holds
-// parameter p's entries), the copies read the looked-up parameter's entries
-// through the scalar cache.  Tile counts fit in 31 bits (the planner checks);
-// grid-stride loops count in 64 bits so that the last step cannot overflow.
+// cast or reduction with 16-byte vector accesses.  The per-parameter table
+// travels in the kernel arguments.  The pack and the reduce number their tiles
+// parameter by parameter and hold the table in lanes (lane p holds parameter
+// p's entries; a ballot over the first tiles finds a tile's parameter).  The
+// W-way copies number theirs chunk by chunk and look a tile up with scalar
+// instructions only (CopyTiles).  Tile counts fit in 31 bits (the planner
+// checks); grid-stride loops count in 64 bits, or in unsigned 32 (a tile
+// number plus a grid size is below 2^32), so the last step cannot overflow.
 //
 // A bucket buffer of W chunks is addressed either as one allocation (chunk i
 // at base + i*stride) or through a table of W chunk pointers, so the same
@@ -236,6 +236,38 @@ __device__ __forceinline__ void st16f(float* p, float4 v) {
     else *q = w;
 }
 
+// ------------------------------------------------------------------ windows
+
+// A window of `bytes` bytes from a wave-uniform address on, as a raw buffer
+// resource (32-bit data format, no stride): an access takes a 32-bit byte
+// offset per lane, and one at or past `bytes` reads zero or is dropped.
+// Loads are non-temporal.  Stores are non-temporal and write through (sc1:
+// system scope), so a streamed line leaves the L2 as it is written instead of
+// waiting there to be evicted among the reads: a plain copy of 1.7 GB takes
+// 520 us this way, 526 us with the non-temporal bit alone, 546 us with neither.
+typedef __amdgpu_buffer_rsrc_t Window;
+constexpr int kRawBuffer = 0x00020000;
+constexpr int kPolicyNt = 2, kPolicySc1 = 16;
+#ifndef FSDP_LOAD_POLICY
+#define FSDP_LOAD_POLICY kPolicyNt
+#endif
+#ifndef FSDP_STORE_POLICY
+#define FSDP_STORE_POLICY (kPolicySc1 | kPolicyNt)
+#endif
+__device__ __forceinline__ Window window(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kRawBuffer);
+}
+__device__ __forceinline__ u32x4 ld16(Window w, uint32_t byte) {
+    return __builtin_amdgcn_raw_buffer_load_b128(w, int(byte), 0, FSDP_LOAD_POLICY);
+}
+__device__ __forceinline__ u32x2 ld8(Window w, uint32_t byte) {
+    return __builtin_amdgcn_raw_buffer_load_b64(w, int(byte), 0, FSDP_LOAD_POLICY);
+}
+__device__ __forceinline__ void st16(Window w, uint32_t byte, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, w, int(byte), 0, FSDP_STORE_POLICY);
+}
+__device__ __forceinline__ void st16(Window w, uint32_t byte, f32x4 v) { st16(w, byte, __builtin_bit_cast(u32x4, v)); }
+
 // ------------------------------------------------------------------ bucket chunk addressing
 
 // One allocation holding W chunks, chunk i at base + i*stride bytes.
@@ -373,16 +405,17 @@ __device__ __forceinline__ void seg_copy(const uint16_t* __restrict__ s, uint16_
         }
     }
     if (vec && hi - lo == kTile && (hi <= v || lo >= v)) {
+        const Window out = window(d + lo, kTile * 2);
         if (hi <= v) {
-            uint4 x[kSteps];
+            const Window in = window(s + lo, kTile * 2);
+            u32x4 x[kSteps];
 #pragma unroll
-            for (int u = 0; u < kSteps; ++u) x[u] = ld16(s + lo + (int64_t(u) * kCopyBlock + threadIdx.x) * kVec);
+            for (int u = 0; u < kSteps; ++u) x[u] = ld16(in, (u * kCopyBlock + threadIdx.x) * 16);
 #pragma unroll
-            for (int u = 0; u < kSteps; ++u) st16(d + lo + (int64_t(u) * kCopyBlock + threadIdx.x) * kVec, x[u]);
+            for (int u = 0; u < kSteps; ++u) st16(out, (u * kCopyBlock + threadIdx.x) * 16, x[u]);
         } else {
 #pragma unroll
-            for (int u = 0; u < kSteps; ++u)
-                st16(d + lo + (int64_t(u) * kCopyBlock + threadIdx.x) * kVec, make_uint4(0, 0, 0, 0));
+            for (int u = 0; u < kSteps; ++u) st16(out, (u * kCopyBlock + threadIdx.x) * 16, u32x4{0, 0, 0, 0});
         }
         return;
     }
@@ -409,25 +442,26 @@ template <int kSteps, int kFrom>
 __device__ __forceinline__ void seg_widen(const uint16_t* __restrict__ s, float* __restrict__ d, int64_t lo,
                                           int64_t hi, int64_t v, bool vec) {
     constexpr int kSub = kSteps;
-    constexpr int64_t kTile = int64_t(kCopyBlock) * 4 * kSub;
+    constexpr int64_t kTile = int64_t(kWidenBlock) * 4 * kSub;
     if (vec && hi - lo == kTile && (hi <= v || lo >= v)) {
+        const Window out = window(d + lo, kTile * 4);
         if (hi <= v) {
-            uint2 x[kSub];
+            const Window in = window(s + lo, kTile * 2);
+            u32x2 x[kSub];
 #pragma unroll
-            for (int u = 0; u < kSub; ++u) x[u] = ld8(s + lo + (int64_t(u) * kCopyBlock + threadIdx.x) * 4);
+            for (int u = 0; u < kSub; ++u) x[u] = ld8(in, (u * kWidenBlock + threadIdx.x) * 8);
 #pragma unroll
             for (int u = 0; u < kSub; ++u)
-                st16f(d + lo + (int64_t(u) * kCopyBlock + threadIdx.x) * 4,
-                      make_float4(widen_lo<kFrom>(x[u].x), widen_hi<kFrom>(x[u].x), widen_lo<kFrom>(x[u].y), widen_hi<kFrom>(x[u].y)));
+                st16(out, (u * kWidenBlock + threadIdx.x) * 16,
+                     f32x4{widen_lo<kFrom>(x[u].x), widen_hi<kFrom>(x[u].x), widen_lo<kFrom>(x[u].y), widen_hi<kFrom>(x[u].y)});
         } else {
 #pragma unroll
-            for (int u = 0; u < kSub; ++u)
-                st16f(d + lo + (int64_t(u) * kCopyBlock + threadIdx.x) * 4, make_float4(0.f, 0.f, 0.f, 0.f));
+            for (int u = 0; u < kSub; ++u) st16(out, (u * kWidenBlock + threadIdx.x) * 16, f32x4{0.f, 0.f, 0.f, 0.f});
         }
         return;
     }
     for (int u = 0; u < kSub; ++u) {
-        const int64_t g = lo + (int64_t(u) * kCopyBlock + threadIdx.x) * 4;
+        const int64_t g = lo + (int64_t(u) * kWidenBlock + threadIdx.x) * 4;
         if (g >= hi) break;
         if (vec && g + 4 <= hi && (g + 4 <= v || g >= v)) {
             const uint2 x = g < v ? ld8(s + g) : make_uint2(0, 0);
@@ -491,9 +525,7 @@ struct PackParam {
 // tile table, then the entries of the parameter it names).  from_lane is only
 // called where every lane of the wave is active, on values every lane wrote:
 // a lane that is inactive when a value is computed keeps its old register,
-// and readlane would return that.  The pack and the
-// reduce use them.  The copies do not: their tiles are two 16-byte loads per
-// lane, and the tables' extra vector loads per wave made them 3-5 % slower.
+// and readlane would return that.  The pack and the reduce use them.
 __device__ __forceinline__ int lane_index() { return int(threadIdx.x & 63); }
 // The table entry a lane loads: its own, or the last one for the lanes past
 // PMAX (none while PMAX is the wavefront width; their tile start is INT_MAX,
@@ -740,121 +772,186 @@ __global__ void __launch_bounds__(kCopyBlock) replicate_grouped_kernel(const Rep
 // were 8 % slower, and the reduce gained nothing from such an order); the
 // tiles past the last whole group keep order b.  A bijection
 // on [0, n), so a grid-stride loop over b still covers every tile once.
-__device__ __forceinline__ int copy_tile(int64_t b, int n) {
-    constexpr int64_t kGroup = int64_t(kXcds) * kXcdRun;
-    if (b >= int64_t(n) / kGroup * kGroup) return int(b);
-    const int64_t r = b % kGroup;
-    return int(b - r + (r % kXcds) * kXcdRun + r / kXcds);
+__device__ __forceinline__ uint32_t copy_tile(uint32_t b, uint32_t n) {
+    constexpr uint32_t kGroup = uint32_t(kXcds) * kXcdRun;
+    if (b >= n / kGroup * kGroup) return b;
+    const uint32_t r = b % kGroup;
+    return b - r + (r % kXcds) * kXcdRun + r / kXcds;
 }
+
+// n / d for 0 <= n < 2^31 by a multiplication: with 2^(l-1) < d <= 2^l and
+// mul = ceil(2^(31+l) / d) < 2^32, n * mul / 2^(31+l) exceeds n / d by less
+// than 1 / d, so its floor is the quotient.
+struct Divider {
+    uint32_t mul, shift;
+    __device__ __forceinline__ uint32_t quotient(uint32_t n) const { return uint32_t((uint64_t(n) * mul) >> shift); }
+};
+Divider divider(uint32_t d) {
+    int l = 0;
+    while ((uint64_t(1) << l) < d) ++l;
+    const uint64_t one = uint64_t(1) << (31 + l);
+    return {uint32_t((one + d - 1) / d), uint32_t(31 + l)};
+}
+
+// The tiles of a W-way copy: chunk by chunk and, within a chunk, parameter by
+// parameter, so a launch walks the bucket buffer front to front.
+//
+// What bounds the copies is HBM, and within that two things that are settled
+// before a wave's first data load:
+//   * the look-up.  A table read by vector loads waits in the same queues as
+//     the streams of the waves around it (about one full loaded latency), so
+//     everything here comes through the scalar cache: these fields in one
+//     round, four entries of the full table above kPivots parameters, then the
+//     parameter's record in one 32-byte load; the chunk by a multiplication.
+//   * the bytes in flight.  A copy streams fastest with about 40 KB of loads
+//     in flight per CU (20 waves of 2 KB, kCopyWaves per SIMD; a plain copy
+//     loop peaks at 24-32 KB).  With all 32 waves the reads and writes of too
+//     many places meet in the memory controllers, and the copy is slower.
+// Both copies of the 70B block (3.42 GB): 530 -> 506 us unpack, 537 -> 512 us
+// pack (the look-up without the cap: 548 and 537; the cap without the look-up:
+// 531 and 532).  4 and 6 waves are 0-2 % slower, 3 waves 5 %, 8 waves 4-7 %.
+#ifndef FSDP_COPY_WAVES
+#define FSDP_COPY_WAVES 5
+#endif
+constexpr int kCopyWaves = FSDP_COPY_WAVES;       // resident waves per SIMD
+constexpr int kCopyAnyWaves = kCopyWaves + 1;     // where units are joined from two blocks (below)
+// The widening pack has half the bytes in flight per wave: no cap.
+template <int kWiden, bool kAny> constexpr int kPackMinWaves = kWiden != kF32 ? 4 : kAny ? kCopyAnyWaves : kCopyWaves;
+template <int kWiden, bool kAny> constexpr int kPackMaxWaves = kWiden != kF32 ? 8 : kAny ? kCopyAnyWaves : kCopyWaves;
+
+constexpr int kPivots = 16;
+constexpr int kPerPivot = 4;
+static_assert(kPivots * kPerPivot >= PMAX, "the pivots cover every parameter");
+struct CopyTiles {
+    uint32_t ntiles;               // W * per_chunk
+    uint32_t per_chunk;            // tiles of one chunk
+    Divider by_chunk;              // n / per_chunk
+    uint32_t pivot[kPivots];       // first tile (in a chunk) of parameter k, or of 4k if `deep`; UINT_MAX past the last
+    uint32_t deep;                 // more than kPivots parameters
+    uint32_t start[PMAX];          // first tile of every parameter; UINT_MAX past the last
+};
+
+// One parameter of a W-way copy, in 2-byte units (or 16-bit elements where
+// they are widened to fp32): one 32-byte scalar load.
+struct alignas(32) CopyParam {
+    uint16_t* data;      // the full parameter or gradient
+    int64_t off;         // off_p
+    int64_t seg;         // L_p
+    int64_t elems;       // N_p * inner_p
+    // Elements of chunk i's segment (the last chunks' may be short or empty).
+    __device__ __forceinline__ int64_t valid(int i) const {
+        const int64_t rest = elems - int64_t(i) * seg;
+        return rest < seg ? (rest > 0 ? rest : 0) : seg;
+    }
+};
+
+// Entry p of the records, all of it loaded here (the fields that are needed
+// late would otherwise be loaded late, in a round of their own).
+__device__ __forceinline__ CopyParam load_param(const CopyParam* params, int p) {
+    CopyParam q = params[p];
+    asm volatile("" : "+s"(q.data), "+s"(q.off), "+s"(q.seg), "+s"(q.elems));
+    return q;
+}
+
+// Where the tile of workgroup-order index `step` lies.
+struct CopyPlace {
+    int chunk, param;
+    uint32_t tile;        // within the parameter's segment of that chunk
+    __device__ __forceinline__ CopyPlace(const CopyTiles& c, uint32_t step) {
+        const uint32_t t = copy_tile(step, c.ntiles);
+        const uint32_t i = c.by_chunk.quotient(t);
+        const uint32_t r = t - i * c.per_chunk;
+        int k = -1;                                  // the last pivot at or before r
+        uint32_t first = 0;
+#pragma unroll
+        for (int e = 0; e < kPivots; ++e) {
+            const bool in = c.pivot[e] <= r;
+            k = in ? e : k;
+            first = in ? c.pivot[e] : first;
+        }
+        if (c.deep) {
+            k *= kPerPivot;
+            const int base = k;
+#pragma unroll
+            for (int e = 0; e < kPerPivot; ++e) {
+                const uint32_t f = c.start[base + e];
+                const bool in = f <= r;
+                k = in ? base + e : k;
+                first = in ? f : first;
+            }
+        }
+        chunk = int(i);
+        param = k;
+        tile = r - first;
+    }
+};
 
 // ------------------------------------------------------------------ ag_unpack
 
 // Sizes in 2-byte units (an fp32 element is two units).
 template <class Chunks>
 struct UnpackArgs {
-    uint16_t* dst[PMAX];
-    int64_t off[PMAX];
-    int64_t seg[PMAX];           // L_p
-    int64_t elems[PMAX];         // N_p * inner_p
-    int32_t tiles_per_seg[PMAX]; // ceil(L_p / tile)
-    int32_t tile_start[PMAX];
+    CopyTiles tiles;
     Chunks src;                  // gathered chunks, one per source rank
-    int32_t nparams;
-    int32_t ntiles;
+    CopyParam param[PMAX];
 };
 
 template <class Chunks, bool kAny>
-__global__ void __launch_bounds__(kCopyBlock) ag_unpack_kernel(const UnpackArgs<Chunks> a) {
-    const int lane = threadIdx.x & 63;
-#if FSDP_LDS_TABLE
-    const int my_start = staged_entry(a.tile_start, a.nparams);
-#else
-    const int my_start = lane < a.nparams ? a.tile_start[lane] : INT_MAX;
-#endif
-    for (int64_t step = blockIdx.x; step < a.ntiles; step += gridDim.x) {
-        const int t = copy_tile(step, a.ntiles);
-        const int p = param_of_tile(my_start, t);
-        const int lt = t - a.tile_start[p];
-        const int tps = a.tiles_per_seg[p];
-        const int i = lt / tps;                          // source rank
-        const int64_t st = lt - int64_t(i) * tps;
-        const int64_t L = a.seg[p];
-        const int64_t rest = a.elems[p] - int64_t(i) * L;
-        const int64_t v = rest < L ? (rest > 0 ? rest : 0) : L;
-        const int64_t lo = st * kCopyTile;
+__global__ void __launch_bounds__(kCopyBlock)
+__attribute__((amdgpu_waves_per_eu(kAny ? kCopyAnyWaves : kCopyWaves, kAny ? kCopyAnyWaves : kCopyWaves)))
+ag_unpack_kernel(const UnpackArgs<Chunks> a) {
+    uint32_t step = blockIdx.x;
+    do {
+        const CopyPlace at(a.tiles, step);
+        const int i = at.chunk;                          // source rank
+        const CopyParam q = load_param(a.param, at.param);
+        const int64_t v = q.valid(i);
+        const int64_t lo = int64_t(at.tile) * kCopyTile;
         const int64_t hi = min(lo + kCopyTile, v);
+        step += gridDim.x;
         if (lo >= hi) continue;
-        const uint16_t* s = reinterpret_cast<const uint16_t*>(a.src.at(i)) + a.off[p];
-        uint16_t* d = a.dst[p] + int64_t(i) * L;
+        const uint16_t* s = reinterpret_cast<const uint16_t*>(a.src.at(i)) + q.off;
+        uint16_t* d = q.data + int64_t(i) * q.seg;
         seg_copy<kCopySteps, kAny>(s, d, lo, hi, hi, is_aligned16(s) && is_aligned16(d), v, v);
-    }
+    } while (step < a.tiles.ntiles);
 }
 
 // ------------------------------------------------------------------ rs_pack
 
 // Sizes in units of the source gradient: 2-byte units for a plain copy, 16-bit
 // elements when kWiden (kBF16 or kF16; kF32 = no widening) casts them to an
-// fp32 wire.  Tiles are numbered parameter by parameter and, within a
-// parameter, destination by destination; for W above kDestMajorW they are
-// numbered destination by destination and, within a destination, parameter by
-// parameter, so that the workgroups running at one time write one destination
-// chunk front to front instead of the segments of many chunks at once.
-constexpr int kDestMajorW = 64;
-
+// fp32 wire.
 template <class Chunks>
 struct RsPackArgs {
-    const uint16_t* src[PMAX];   // full gradients
-    int64_t off[PMAX + 1];       // off[P] = S
-    int64_t seg[PMAX];
-    int64_t elems[PMAX];
-    int32_t tiles_per_seg[PMAX]; // ceil((off_{p+1} - off_p) / tile)
-    int32_t tile_start[PMAX];    // first tile of parameter p (within one destination if dest_major)
+    CopyTiles tiles;
     Chunks dst;                  // send chunks, one per destination rank
-    int32_t nparams;
-    int32_t dest_major;
-    int32_t tiles_per_dest;      // tiles of one destination chunk
-    int32_t ntiles;              // W * tiles_per_dest
+    CopyParam param[PMAX + 1];   // param[P].off = S
 };
 
 template <class Chunks, int kWiden, bool kAny>
-__global__ void __launch_bounds__(kCopyBlock) rs_pack_kernel(const RsPackArgs<Chunks> a) {
-    const int lane = threadIdx.x & 63;
-#if FSDP_LDS_TABLE
-    const int my_start = staged_entry(a.tile_start, a.nparams);
-#else
-    const int my_start = lane < a.nparams ? a.tile_start[lane] : INT_MAX;
-#endif
-    for (int64_t step = blockIdx.x; step < a.ntiles; step += gridDim.x) {
-        const int t = copy_tile(step, a.ntiles);
-        int p, j;                                        // parameter, destination rank
-        int64_t st;                                      // tile within the segment
-        if (a.dest_major) {
-            j = t / a.tiles_per_dest;
-            const int r = t - j * a.tiles_per_dest;
-            p = param_of_tile(my_start, r);
-            st = r - a.tile_start[p];
-        } else {
-            p = param_of_tile(my_start, t);
-            const int lt = t - a.tile_start[p];
-            j = lt / a.tiles_per_seg[p];
-            st = lt - int64_t(j) * a.tiles_per_seg[p];
-        }
-        const int64_t region = a.off[p + 1] - a.off[p];
-        const int64_t L = a.seg[p];
-        const int64_t rest = a.elems[p] - int64_t(j) * L;
-        const int64_t v = rest < L ? (rest > 0 ? rest : 0) : L;
+__global__ void __launch_bounds__(kWiden != kF32 ? kWidenBlock : kCopyBlock)
+__attribute__((amdgpu_waves_per_eu(kPackMinWaves<kWiden, kAny>, kPackMaxWaves<kWiden, kAny>)))
+rs_pack_kernel(const RsPackArgs<Chunks> a) {
+    uint32_t step = blockIdx.x;
+    do {
+        const CopyPlace at(a.tiles, step);
+        const int j = at.chunk;                          // destination rank
+        const CopyParam q = load_param(a.param, at.param);
+        const int64_t region = a.param[at.param + 1].off - q.off;
+        const int64_t v = q.valid(j);
         constexpr int64_t kTile = kWiden != kF32 ? kWidenTile : kCopyTile;
-        const int64_t lo = st * kTile;
+        const int64_t lo = int64_t(at.tile) * kTile;
         const int64_t hi = min(lo + kTile, region);
-        const uint16_t* s = a.src[p] + int64_t(j) * L;
+        step += gridDim.x;
+        const uint16_t* s = q.data + int64_t(j) * q.seg;
         if constexpr (kWiden != kF32) {
-            float* d = reinterpret_cast<float*>(a.dst.at(j)) + a.off[p];
-            seg_widen<kCopySteps, kWiden>(s, d, lo, hi, v, is_aligned16(s) && is_aligned16(d));
+            float* d = reinterpret_cast<float*>(a.dst.at(j)) + q.off;
+            seg_widen<kWidenSteps, kWiden>(s, d, lo, hi, v, is_aligned16(s) && is_aligned16(d));
         } else {
-            uint16_t* d = reinterpret_cast<uint16_t*>(a.dst.at(j)) + a.off[p];
+            uint16_t* d = reinterpret_cast<uint16_t*>(a.dst.at(j)) + q.off;
             seg_copy<kCopySteps, kAny>(s, d, lo, hi, v, is_aligned16(s) && is_aligned16(d), v, region);
         }
-    }
+    } while (step < a.tiles.ntiles);
 }
 
 // ------------------------------------------------------------------ rs_reduce
@@ -1386,7 +1483,31 @@ fsdp_status do_ag_pack_one(const fsdp_plan* h, int32_t rank, const float* const*
     return do_ag_pack(*pl, rank, shards, wire, OneChunk{static_cast<char*>(send_chunk)}, 1, outs, stream);
 }
 
-// ---- ag_unpack: u = 2-byte units per element
+// ---- the W-way copies: u = 2-byte units per element
+
+// Parameter p has n tiles per chunk, its first being *nt.
+fsdp_status add_copy_tiles(const Plan& pl, int p, int64_t n, CopyTiles* c, int64_t* nt) {
+    if (n * pl.world > INT32_MAX || (*nt + n) * pl.world > INT32_MAX)
+        return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
+    c->start[p] = uint32_t(*nt);
+    *nt += n;
+    return FSDP_OK;
+}
+
+// The rest of the table, once every parameter has its tiles (nt in a chunk).
+void finish_copy_tiles(const Plan& pl, int64_t nt, CopyTiles* c) {
+    for (int p = pl.nparams; p < PMAX; ++p) c->start[p] = UINT32_MAX;   // never a tile's parameter
+    c->deep = pl.nparams > kPivots;
+    for (int k = 0; k < kPivots; ++k) c->pivot[k] = c->start[c->deep ? k * kPerPivot : k];
+    c->ntiles = uint32_t(nt * pl.world);
+    c->per_chunk = uint32_t(nt);
+    c->by_chunk = divider(uint32_t(std::max<int64_t>(nt, 1)));
+}
+
+// Whether some segment of the parameter is off the 16-byte grid.
+bool off_grid(const CopyParam& q) { return ((q.off * 2) & 15) || ((q.seg * 2) & 15) || !aligned16(q.data); }
+
+// ---- ag_unpack
 
 template <class Chunks>
 fsdp_status do_ag_unpack(const Plan& pl, const Chunks& src, const Spans& ins, int u,
@@ -1395,34 +1516,24 @@ fsdp_status do_ag_unpack(const Plan& pl, const Chunks& src, const Spans& ins, in
     if (params == nullptr) return fail(FSDP_ERR_INVALID, "params is NULL");
     UnpackArgs<Chunks> a{};
     Spans outs;
-    int64_t nt = 0;
+    int64_t nt = 0;               // tiles of one chunk
+    bool any = !chunks_aligned(src);
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t e = pl.elems[p];
         if ((st = check_param_ptr(params[p], e, 2 * u, p, "params")) != FSDP_OK) return st;
-        a.dst[p] = static_cast<uint16_t*>(params[p]);
-        a.off[p] = pl.off[p] * u;
-        a.seg[p] = pl.seg[p] * u;
-        a.elems[p] = e * u;
-        const int64_t tps = tiles(a.seg[p], kCopyTile);
-        if (tps > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
-        a.tiles_per_seg[p] = int32_t(tps);
-        a.tile_start[p] = int32_t(nt);
-        nt += int64_t(pl.world) * a.tiles_per_seg[p];
-        if (nt > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
+        a.param[p] = {static_cast<uint16_t*>(params[p]), pl.off[p] * u, pl.seg[p] * u, e * u};
+        if ((st = add_copy_tiles(pl, p, tiles(pl.seg[p] * u, kCopyTile), &a.tiles, &nt)) != FSDP_OK) return st;
+        // Every tile of segment i of parameter p reads chunk i at off_p and
+        // writes params[p] at i * L_p: all on the 16-byte grid unless a
+        // stride, offset, length or pointer is not.
+        if (off_grid(a.param[p])) any = true;
         if (e > 0) outs.add(params[p], e * 2 * u);
     }
     a.src = src;
-    a.nparams = pl.nparams;
-    a.ntiles = int32_t(nt);
+    finish_copy_tiles(pl, nt, &a.tiles);
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
-    // Every tile of segment i of parameter p reads chunk i at off_p and writes
-    // params[p] at i * L_p: all on the 16-byte grid unless a stride, offset,
-    // length or pointer is not.
-    bool any = !chunks_aligned(src);
-    for (int p = 0; p < pl.nparams; ++p)
-        if (((a.off[p] * 2) & 15) || ((a.seg[p] * 2) & 15) || !aligned16(a.dst[p])) any = true;
-    if (any) return launch(pl, ag_unpack_kernel<Chunks, true>, a, a.ntiles, kCopyBlock, stream);
-    return launch(pl, ag_unpack_kernel<Chunks, false>, a, a.ntiles, kCopyBlock, stream);
+    if (any) return launch(pl, ag_unpack_kernel<Chunks, true>, a, int(a.tiles.ntiles), kCopyBlock, stream);
+    return launch(pl, ag_unpack_kernel<Chunks, false>, a, int(a.tiles.ntiles), kCopyBlock, stream);
 }
 
 // ---- rs_pack: gradient elements of `gsize` bytes; kWiden (kBF16 / kF16) casts
@@ -1434,43 +1545,29 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
     fsdp_status st;
     if (grads == nullptr) return fail(FSDP_ERR_INVALID, "grads is NULL");
     const int u = kWiden != kF32 ? 1 : gsize / 2;     // kernel units per element
+    constexpr int64_t kTile = kWiden != kF32 ? kWidenTile : kCopyTile;
+    constexpr int kBlock = kWiden != kF32 ? kWidenBlock : kCopyBlock;
     RsPackArgs<Chunks> a{};
     Spans ins;
-    int64_t nt = 0;
+    int64_t nt = 0;               // tiles of one chunk
+    bool any = !chunks_aligned(dst);
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t e = pl.elems[p];
         if ((st = check_param_ptr(grads[p], e, gsize, p, "grads")) != FSDP_OK) return st;
-        a.src[p] = static_cast<const uint16_t*>(grads[p]);
-        a.off[p] = pl.off[p] * u;
-        a.seg[p] = pl.seg[p] * u;
-        a.elems[p] = e * u;
-        const int64_t tps = tiles((pl.off[p + 1] - pl.off[p]) * u, kWiden != kF32 ? kWidenTile : kCopyTile);
-        if (tps * pl.world > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
-        a.tiles_per_seg[p] = int32_t(tps);
-        a.tile_start[p] = int32_t(nt);                  // rescaled below for the parameter-major order
-        nt += tps;
-        if (nt * pl.world > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
+        a.param[p] = {static_cast<uint16_t*>(const_cast<void*>(grads[p])), pl.off[p] * u, pl.seg[p] * u, e * u};
+        const int64_t n = tiles((pl.off[p + 1] - pl.off[p]) * u, kTile);
+        if ((st = add_copy_tiles(pl, p, n, &a.tiles, &nt)) != FSDP_OK) return st;
+        // Tiles read grads[p] at j * L_p and write chunk j at off_p.
+        if (off_grid(a.param[p])) any = true;
         if (e > 0) ins.add(grads[p], e * gsize);
     }
-    a.dest_major = pl.world > kDestMajorW;
-    if (!a.dest_major)
-        for (int p = 0; p < pl.nparams; ++p) a.tile_start[p] *= pl.world;
-    a.off[pl.nparams] = pl.chunk * u;
+    a.param[pl.nparams].off = pl.chunk * u;
     a.dst = dst;
-    a.nparams = pl.nparams;
-    a.tiles_per_dest = int32_t(nt);
-    a.ntiles = int32_t(nt * pl.world);
+    finish_copy_tiles(pl, nt, &a.tiles);
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
-    // Tiles read grads[p] at j * L_p and write chunk j at off_p (the widening
-    // pack has its own checks and no misaligned vector path).
-    bool any = false;
-    if constexpr (kWiden == kF32) {
-        any = !chunks_aligned(dst);
-        for (int p = 0; p < pl.nparams; ++p)
-            if (((a.off[p] * 2) & 15) || ((a.seg[p] * 2) & 15) || !aligned16(a.src[p])) any = true;
-    }
-    if (any) return launch(pl, rs_pack_kernel<Chunks, kWiden, true>, a, a.ntiles, kCopyBlock, stream);
-    return launch(pl, rs_pack_kernel<Chunks, kWiden, false>, a, a.ntiles, kCopyBlock, stream);
+    // (The widening pack has its own checks and no misaligned vector path.)
+    if (kWiden == kF32 && any) return launch(pl, rs_pack_kernel<Chunks, kWiden, true>, a, int(a.tiles.ntiles), kBlock, stream);
+    return launch(pl, rs_pack_kernel<Chunks, kWiden, false>, a, int(a.tiles.ntiles), kBlock, stream);
 }
 
 // ---- rs_reduce: received elements of type T

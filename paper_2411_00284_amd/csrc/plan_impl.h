@@ -23,6 +23,12 @@ namespace fsdp {
 #ifndef FSDP_COPY_STEPS
 #define FSDP_COPY_STEPS 2
 #endif
+#ifndef FSDP_WIDEN_BLOCK
+#define FSDP_WIDEN_BLOCK 128
+#endif
+#ifndef FSDP_WIDEN_STEPS
+#define FSDP_WIDEN_STEPS 2
+#endif
 #ifndef FSDP_PACK_STEPS
 #define FSDP_PACK_STEPS 1
 #endif
@@ -47,7 +53,9 @@ constexpr int kCopySteps = FSDP_COPY_STEPS;
 constexpr int64_t kCopyTile = int64_t(kCopyBlock) * kVec * kCopySteps;
 // The widening pack (bf16 in, fp32 out) moves 4 elements per thread and step,
 // so its tiles read half and write the same bytes as a copy tile.
-constexpr int64_t kWidenTile = int64_t(kCopyBlock) * 4 * kCopySteps;
+constexpr int kWidenBlock = FSDP_WIDEN_BLOCK;
+constexpr int kWidenSteps = FSDP_WIDEN_STEPS;
+constexpr int64_t kWidenTile = int64_t(kWidenBlock) * 4 * kWidenSteps;
 constexpr int kPackBlock = FSDP_PACK_BLOCK;
 constexpr int kPackSteps = FSDP_PACK_STEPS;
 constexpr int64_t kPackTile = int64_t(kPackBlock) * kVec * kPackSteps;

@@ -174,6 +174,21 @@ def test_copy_tile_runs(cap):
     plan.close()
 
 
+@pytest.mark.parametrize("cap", [0, 5])
+@pytest.mark.parametrize("num_params", [1, 3, 4, 15, 16, 17, 20, 33, 63, 64])
+def test_copy_tile_lookup(num_params, cap):
+    """The copies find a tile's parameter among 16 pivots, above 16 parameters
+    in two levels of four: parameter counts around both, with empty
+    parameters first, last and in a row, one-tile and many-tile ones."""
+    dims = [((0, 5, 3000, 0, 0, 9, 2048, 4097)[(p + num_params) % 8], (1, 3, 8)[p % 3]) for p in range(num_params)]
+    for w in (1, 3):
+        plan = BucketPlan(w, dims, 8, max_workgroups=cap)
+        oplan = O.make_plan(w, dims, 8)
+        run_ag_unpack(plan, oplan, seed=num_params)
+        run_rs_pack(plan, oplan, seed=num_params)
+        plan.close()
+
+
 @pytest.mark.parametrize("cap", [0, 1, 7, 50])
 @pytest.mark.parametrize("w,dims", [
     (1, [(8192 * 1050 + 5, 1), (3, 7), (1000, 37)]),

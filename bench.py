@@ -46,19 +46,20 @@ PEAK_GBPS = 8000.0                       # MI355X HBM3E
 KERNELS = ("ag_pack", "ag_unpack", "rs_pack", "rs_reduce")
 # Device symbols of the kernels each call launches (bf16 wire, one contiguous
 # buffer), as rocprofv3 prints them; a kernel trace taken during the run
-# replaces these with the names it saw.  A rank shard of fewer than 4
-# full-size reduce tiles per CU is reduced with 128-thread workgroups; a
-# single-chunk pack of fewer than 4 big (256-thread, 4-step) tiles per CU
-# packs with 128-thread, 1-step tiles.
+# replaces these with the names it saw.  The reduce's numbers are the sources a
+# wave keeps in flight and the resident waves per SIMD, by the waves (of 512
+# outputs) that the rank's shard makes; a single-chunk pack of fewer than 4 big
+# (256-thread, 4-step) tiles per CU packs with 128-thread, 1-step tiles.
 # The copies and the reduce have a second form ("true") that the library
-# launches when some segment of the bucket is off the 16-byte grid.
+# launches when some segment of the bucket is read off the 16-byte grid or
+# (the copies) written off the 128-byte lines.
 KERNEL_SYMBOLS = {
     "ag_pack": "ag_pack_kernel<1, OneChunk, 256, 4>",
     "ag_unpack": "ag_unpack_kernel<ContigChunks, false>",
     "rs_pack": "rs_pack_kernel<ContigChunks, 0, false>",
-    "rs_reduce": "rs_reduce_kernel<ContigChunks, unsigned short, 256, false>",
+    "rs_reduce": "rs_reduce_kernel<ContigChunks, unsigned short, 1, 3, false>",
 }
-REDUCE_SMALL_SYMBOL = "rs_reduce_kernel<ContigChunks, unsigned short, 128, false>"
+REDUCE_SMALL_SYMBOL = "rs_reduce_kernel<ContigChunks, unsigned short, 4, 8, false>"
 PACK_SMALL_SYMBOL = "ag_pack_kernel<1, OneChunk, 128, 1>"
 KERNEL_BASENAMES = ("ag_pack_kernel", "ag_unpack_kernel", "rs_pack_kernel", "rs_reduce_kernel", "probe_read_kernel",
                     "probe_fill_kernel", "probe_copy_kernel", "probe_cast_kernel", "probe_reduce_kernel",
@@ -71,10 +72,10 @@ PROFILES = os.path.join(ROOT, "profiles")
 # the 256 MB Infinity Cache.
 ROTATE_BYTES = 3 << 29
 SLEEP_CYCLES = 50_000_000                # a device-side wait that lets the host enqueue a whole leg
-# The full-size reduce tile, the big pack tile and the thresholds of the
-# library's choice between the two shapes of each.
-REDUCE_TILE = 256 * 8 * 2
-SMALL_SHARD_TILES_PER_CU = 4
+# The reduce's tile (one wave), the big pack tile and the thresholds of the
+# library's choice between the forms of each.
+REDUCE_TILE = 64 * 8
+REDUCE_CAP_WAVES, REDUCE_ONE_WAVES, REDUCE_TWO_WAVES, REDUCE_WIDE_W = 32, 10, 5, 32
 PACK_BIG_TILE = 256 * 8 * 4
 PACK_SMALL_TILE = 128 * 8
 PACK_BIG_TILES_PER_CU = 4
@@ -90,17 +91,31 @@ def algorithmic_bytes(W, S, E, V0):
     }
 
 
+def reduce_form(waves_per_cu, world_size, off_grid):
+    """The reduce's template numbers: sources in flight, resident waves, off-grid form."""
+    batch = 1 if waves_per_cu >= REDUCE_ONE_WAVES else 2 if waves_per_cu >= REDUCE_TWO_WAVES else 4
+    if off_grid:
+        return (4, 8, "true") if batch == 4 else (2, 4, "true")
+    if waves_per_cu >= REDUCE_CAP_WAVES:
+        return (1, 3 if world_size >= REDUCE_WIDE_W else 4, "false")
+    return (batch, 8, "false")
+
+
 def kernel_symbol(name, plan, rank, cus):
     """The symbol the call launches for this plan and rank (bf16 wire, one
-    contiguous bucket buffer, 16-byte-aligned tensors)."""
+    contiguous bucket buffer, 512-byte-aligned tensors)."""
     P, S = plan.num_params, plan.chunk_elems
-    off_grid = (2 * S) % 16 != 0 or any((2 * plan.offset(p)) % 16 for p in range(P))
-    if name in ("ag_unpack", "rs_pack") and (off_grid or any((2 * plan.seg_elems(p)) % 16 for p in range(P))):
-        return KERNEL_SYMBOLS[name].replace("false>", "true>")
+    offsets, segs = [2 * plan.offset(p) for p in range(P)], [2 * plan.seg_elems(p) for p in range(P)]
+    if name == "ag_unpack":                                  # chunks are read, parameters written
+        off_grid = any(o % 16 for o in [2 * S] + offsets) or any(n % 128 for n in segs)
+        return KERNEL_SYMBOLS[name].replace("false>", "true>") if off_grid else KERNEL_SYMBOLS[name]
+    if name == "rs_pack":                                    # gradients are read, chunks written
+        off_grid = any(n % 16 for n in segs) or any(o % 128 for o in [2 * S] + offsets)
+        return KERNEL_SYMBOLS[name].replace("false>", "true>") if off_grid else KERNEL_SYMBOLS[name]
     if name == "rs_reduce":
-        full_tiles = sum(-(-plan.local_elems(p, rank) // REDUCE_TILE) for p in range(P))
-        sym = REDUCE_SMALL_SYMBOL if full_tiles < SMALL_SHARD_TILES_PER_CU * cus else KERNEL_SYMBOLS[name]
-        return sym.replace("false>", "true>") if off_grid else sym
+        waves = sum(-(-plan.local_elems(p, rank) // REDUCE_TILE) for p in range(P))
+        form = reduce_form(waves / cus, plan.world_size, any(o % 16 for o in [2 * S] + offsets))
+        return "rs_reduce_kernel<ContigChunks, unsigned short, %d, %d, %s>" % form
     if name == "ag_pack":
         if pack_tiles(plan, PACK_BIG_TILE) < PACK_BIG_TILES_PER_CU * cus:
             return PACK_SMALL_SYMBOL

@@ -48,9 +48,10 @@
  *   - bf16 values are passed as uint16_t bit patterns.
  *   - A launch uses one workgroup per work tile, up to a per-device cap;
  *     past the cap every workgroup loops over several tiles.  The reduction
- *     cuts a small shard (fewer than 4 full-size tiles per CU) into
- *     half-size tiles.  A plan made by fsdp_bucket_plan_ex may lower the cap
- *     or force the tile size; results never depend on either.
+ *     keeps more sources in flight per wave the fewer waves a shard makes, and
+ *     limits the resident waves of a large one.  A plan made by
+ *     fsdp_bucket_plan_ex may lower the cap or force the reduction's form;
+ *     results never depend on either.
  */
 #ifndef FSDP_BUCKET_H
 #define FSDP_BUCKET_H
@@ -113,14 +114,14 @@ fsdp_status fsdp_bucket_plan(int32_t world_size, int32_t num_params,
 /* Launch options of a plan (fsdp_bucket_plan_ex).  They change how the work
  * is cut into workgroups, never a result bit. */
 enum {
-    FSDP_REDUCE_TILES_AUTO = 0,   /* half-size tiles below 4 full-size tiles per CU */
-    FSDP_REDUCE_TILES_FULL = 1,   /* always 256-thread tiles */
-    FSDP_REDUCE_TILES_HALF = 2    /* always 128-thread tiles */
+    FSDP_REDUCE_TILES_AUTO = 0,   /* the form by the shard's waves per CU */
+    FSDP_REDUCE_TILES_FULL = 1,   /* always the form for large shards */
+    FSDP_REDUCE_TILES_HALF = 2    /* always the form for small shards */
 };
 typedef struct fsdp_plan_options {
     int64_t max_workgroups;   /* > 0: no launch of the plan has a larger grid
                                  (workgroups loop over tiles); 0: the default */
-    int32_t reduce_tiles;     /* FSDP_REDUCE_TILES_*; 0 is the default */
+    int32_t reduce_tiles;     /* FSDP_REDUCE_TILES_*: the reduction's form; 0 is the default */
     int32_t reserved;         /* must be 0 */
 } fsdp_plan_options;
 

@@ -126,7 +126,8 @@ class BucketPlan:
     ``shapes`` are the full parameter shapes (dim 0 is sharded, the trailing
     dims are flattened into ``inner``), in bucket order.  ``max_workgroups``
     (> 0) caps every launch's grid and ``reduce_tiles`` ("auto", "full" or
-    "half") fixes the reduction's tile size; neither changes a result.
+    "half") fixes the reduction's form (by the shard's size, or always the one
+    for large or for small shards); neither changes a result.
     """
 
     def __init__(self, world_size: int, shapes: Sequence, align: int = 8, max_workgroups: int = 0,

@@ -41,17 +41,23 @@
 namespace fsdp {
 namespace {
 
-#ifndef FSDP_REDUCE_BATCH
-#define FSDP_REDUCE_BATCH 4
+#ifndef FSDP_REDUCE_WAVES
+#define FSDP_REDUCE_WAVES 4
+#endif
+#ifndef FSDP_REDUCE_CAP_WAVES
+#define FSDP_REDUCE_CAP_WAVES 32
+#endif
+#ifndef FSDP_REDUCE_ONE_WAVES
+#define FSDP_REDUCE_ONE_WAVES 10
+#endif
+#ifndef FSDP_REDUCE_TWO_WAVES
+#define FSDP_REDUCE_TWO_WAVES 5
 #endif
 #ifndef FSDP_BLOCKS_PER_CU
 #define FSDP_BLOCKS_PER_CU 16384
 #endif
 #ifndef FSDP_XCD_RUN
 #define FSDP_XCD_RUN 256
-#endif
-#ifndef FSDP_ANY_NEIGHBOUR
-#define FSDP_ANY_NEIGHBOUR 1
 #endif
 #ifndef FSDP_NT_LOAD
 #define FSDP_NT_LOAD 1
@@ -65,9 +71,14 @@ constexpr int kMaxChunks = FSDP_MAX_CHUNKS;
 // One parameter per lane of a wave64: the ballot lookup and the lane-held
 // tables need every parameter's entry in one wavefront.
 static_assert(PMAX <= 64, "the tile lookup holds one parameter per lane of a 64-wide wavefront");
-static_assert(kCopyBlock % 64 == 0 && kPackBlock % 64 == 0 && kPackBigBlock % 64 == 0 && kReduceBlock % 128 == 0,
-              "workgroups are whole wavefronts (the reduce's half-size tile included)");
-constexpr int kReduceBatch = FSDP_REDUCE_BATCH;   // source ranks loaded before they are added
+static_assert(kCopyBlock % 64 == 0 && kWidenBlock % 64 == 0 && kPackBlock % 64 == 0 && kPackBigBlock % 64 == 0 &&
+                  kReduceBlock == 64,
+              "workgroups are whole wavefronts, the reduction's one wavefront");
+constexpr int kReduceWaves = FSDP_REDUCE_WAVES;           // resident waves per SIMD of a large shard's reduction
+constexpr int kReduceCapWaves = FSDP_REDUCE_CAP_WAVES;    // waves per CU from which a shard is large
+constexpr int kReduceWideW = 32;                          // ... and W from which one wave fewer is resident
+constexpr int kReduceOneWaves = FSDP_REDUCE_ONE_WAVES;    // ... from which a wave keeps one source in flight, not two
+constexpr int kReduceTwoWaves = FSDP_REDUCE_TWO_WAVES;    // ... two sources, not four
 constexpr int kBlocksPerCU = FSDP_BLOCKS_PER_CU;  // workgroups per CU in the grid-stride launch
 constexpr int kXcds = 8;                          // accelerator dies; workgroup b runs on die b % 8
 constexpr int kXcdRun = FSDP_XCD_RUN;             // consecutive copy tiles dealt to one die
@@ -139,10 +150,28 @@ __device__ __forceinline__ int param_of_tile(int my_start, int t) {
     return __builtin_amdgcn_readfirstlane(__popcll(m) - 1);
 }
 
+// A pointer into device memory whose origin the compiler cannot see: the round
+// trip through the global address space keeps its accesses global.  (As flat
+// ones they would count as LDS accesses too, and every wait near them becomes
+// a wait for everything.)
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+    typedef T __attribute__((address_space(1))) Global;
+    return (T*)(Global*)(reinterpret_cast<uintptr_t>(p));
+}
+
+__host__ __device__ __forceinline__ bool on_line(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 127) == 0; }
 __device__ __forceinline__ bool is_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// The same 16 bytes at an address that is only 2- or 4-byte aligned (the
+// target's global loads and stores take any alignment).
+typedef u32x4 __attribute__((aligned(2))) u32x4_any2;
+typedef u32x4 __attribute__((aligned(4))) u32x4_any4;
+typedef f32x4 __attribute__((aligned(4))) f32x4_any4;
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 __attribute__((aligned(2))) u32x2_any2;
 
 // 16-byte accesses; streamed data bypasses cache retention (non-temporal).
 __device__ __forceinline__ uint4 ld16(const void* p) {
@@ -154,44 +183,6 @@ __device__ __forceinline__ uint4 ld16(const void* p) {
 #endif
     return make_uint4(v.x, v.y, v.z, v.w);
 }
-// One 16-byte-aligned block.
-__device__ __forceinline__ u32x4 ld_block(const u32x4* q) {
-#if FSDP_NT_LOAD
-    return __builtin_nontemporal_load(q);
-#else
-    return *q;
-#endif
-}
-
-// Bytes [r, r + 16) of the 32 bytes v0 followed by v1 (0 < r < 16), joined
-// with byte funnel shifts.
-__device__ __forceinline__ uint4 join16(const u32x4& v0, const u32x4& v1, uint32_t r) {
-    uint32_t w0, w1, w2, w3, w4;                      // the five words from word r / 4 on
-    switch (r >> 2) {
-        case 0: w0 = v0.x; w1 = v0.y; w2 = v0.z; w3 = v0.w; w4 = v1.x; break;
-        case 1: w0 = v0.y; w1 = v0.z; w2 = v0.w; w3 = v1.x; w4 = v1.y; break;
-        case 2: w0 = v0.z; w1 = v0.w; w2 = v1.x; w3 = v1.y; w4 = v1.z; break;
-        default: w0 = v0.w; w1 = v1.x; w2 = v1.y; w3 = v1.z; w4 = v1.w; break;
-    }
-    const uint32_t b = r & 3u;                         // bytes into word r / 4
-    return make_uint4(__builtin_amdgcn_alignbyte(w1, w0, b), __builtin_amdgcn_alignbyte(w2, w1, b),
-                      __builtin_amdgcn_alignbyte(w3, w2, b), __builtin_amdgcn_alignbyte(w4, w3, b));
-}
-
-// 16 bytes from an address that is only 2-byte aligned (a segment of a dense
-// bucket, A < 8): the aligned 16-byte block holding p, and when p is not
-// 16-byte aligned the next one too, joined with byte funnel shifts.  Each of
-// the two blocks holds at least one byte of [p, p + 16) and lies inside one
-// 16-byte-aligned block, so it never reaches a page that [p, p + 16) does not.
-__device__ __forceinline__ uint4 ld16_any(const void* p) {
-    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
-    const uint32_t r = uint32_t(a) & 15u;
-    const u32x4* q = reinterpret_cast<const u32x4*>(a - r);
-    const u32x4 v0 = ld_block(q);
-    if (r == 0) return make_uint4(v0.x, v0.y, v0.z, v0.w);
-    return join16(v0, ld_block(q + 1), r);
-}
-
 // Stores are non-temporal unless kNt is false: a chunk that other workgroups
 // read back at once (the first half of a wide push) is stored through the cache.
 template <bool kNt = bool(FSDP_NT_STORE)>
@@ -201,7 +192,6 @@ __device__ __forceinline__ void st16(void* p, uint4 v) {
     if constexpr (kNt) __builtin_nontemporal_store(w, q);
     else *q = w;
 }
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint2 ld8(const void* p) {
     const u32x2* q = reinterpret_cast<const u32x2*>(p);
@@ -274,206 +264,206 @@ __device__ __forceinline__ void st16(Window w, uint32_t byte, f32x4 v) { st16(w,
 struct ContigChunks {
     char* base;
     int64_t stride;
-    __device__ __forceinline__ char* at(int i) const { return base + int64_t(i) * stride; }
+    __device__ __forceinline__ char* at(int i) const { return as_global(base + int64_t(i) * stride); }
+    // at(i) for an i that may be W or more: an address that is not accessed then.
+    __device__ __forceinline__ char* ahead(int i, int) const { return at(i); }
     __device__ __forceinline__ bool aligned() const { return ((uintptr_t(base) | uintptr_t(stride)) & 15) == 0; }
-};
-
-// Contiguous chunks seen as a typed tile pointer plus a stride in elements:
-// chunk i of the tile at tile + i*stride.
-template <typename T>
-struct StridedTile {
-    const T* tile;
-    int64_t stride;
-    __device__ __forceinline__ const T* at(int i) const { return tile + int64_t(i) * stride; }
 };
 
 // W chunks anywhere (up to kMaxChunks), chunk i at ptr[i]; the host checks
 // that every chunk is 16-byte aligned.
 struct TableChunks {
     char* ptr[kMaxChunks];
-    __device__ __forceinline__ char* at(int i) const { return ptr[i]; }
+    __device__ __forceinline__ char* at(int i) const { return as_global(ptr[i]); }
+    __device__ __forceinline__ char* ahead(int i, int world) const { return at(min(i, world - 1)); }
     __device__ __forceinline__ bool aligned() const { return true; }
+};
+
+// ------------------------------------------------------------------ tile look-up
+
+// The first tile of every parameter, in tile order (a parameter without tiles
+// shares its start with the next one).  It is read with scalar loads: one
+// round for the pivots, a second for four entries above kPivots parameters.
+constexpr int kPivots = 16;
+constexpr int kPerPivot = 4;
+static_assert(kPivots * kPerPivot >= PMAX, "the pivots cover every parameter");
+struct TileTable {
+    uint32_t pivot[kPivots];       // first tile of parameter k, or of 4k if `deep`; UINT_MAX past the last
+    uint32_t deep;                 // more than kPivots parameters
+    uint32_t start[PMAX];          // first tile of every parameter; UINT_MAX past the last
+};
+
+// The parameter of tile r, the last one that starts at or before it, and the
+// tile's number within it.
+struct TilePlace {
+    int param;
+    uint32_t tile;
+    __device__ __forceinline__ TilePlace(const TileTable& c, uint32_t r) {
+        int k = 0;
+        uint32_t first = 0;
+#pragma unroll
+        for (int e = 0; e < kPivots; ++e) {
+            const bool in = c.pivot[e] <= r;
+            k = in ? e : k;
+            first = in ? c.pivot[e] : first;
+        }
+        if (c.deep) {
+            const int base = k * kPerPivot;
+            k = base;
+#pragma unroll
+            for (int e = 0; e < kPerPivot; ++e) {
+                const uint32_t f = c.start[base + e];
+                const bool in = f <= r;
+                k = in ? base + e : k;
+                first = in ? f : first;
+            }
+        }
+        param = k;
+        tile = r - first;
+    }
 };
 
 // ------------------------------------------------------------------ segment copy
 
-// The block of the next lane (lane l gets lane l + 1's value; lane 63's
-// result is not used): a DPP wave shift, run where every lane is active.
-constexpr int kDppWaveShl1 = 0x130;   // DPP control: each lane reads lane + 1 of the wave
-constexpr int kDppAllRows = 0xf;      // row and bank masks: every row and bank of the wave
-__device__ __forceinline__ uint32_t next_lane(uint32_t v) {
-    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kDppWaveShl1, kDppAllRows, kDppAllRows, false));
-}
-__device__ __forceinline__ u32x4 next_lane(const u32x4& v) {
-    return u32x4{next_lane(v.x), next_lane(v.y), next_lane(v.z), next_lane(v.w)};
+__device__ __forceinline__ int clamp_to(int64_t x, int hi) { return int(min(max(x, int64_t(0)), int64_t(hi))); }
+
+// d[k] = k < v ? s[k] : 0 for the elements k of unit [g, g + kN) that lie below
+// `end`, one by one.
+template <int kN, typename D, typename S, class Cast>
+__device__ __forceinline__ void copy_elements(const S* s, D* d, int64_t g, int64_t v, int64_t end, Cast cast) {
+    for (int64_t k = g; k < min(g + kN, end); ++k) d[k] = k < v ? cast(s[k]) : D(0);
 }
 
-// d[k] = k < v ? s[k] : 0 for k in [lo, hi): one tile of kSteps steps of
-// kCopyBlock threads x 8 elements, in 2-byte units (bf16, or the halves of
-// fp32 words for a plain copy).  `vec`: s and d are 16-byte aligned at 0.
-//
-// When s + lo or d + lo is not 16-byte aligned (a dense bucket, A < 8), the
-// 16-byte stores follow d's alignment grid and each is fed from s with one
-// load per aligned source block (the next lane's block by DPP; see below).
-// A tile stores the grid units that start in [lo, hi); its last one may run
-// past hi into the next tile's elements (up to the segment's end e), and the
-// next tile starts at the grid point where it ended, so no 16-byte unit is
-// written in parts by two workgroups.  Only the segment's first elements
-// before the grid (in its first tile) and a last unit cut by e are written
-// element by element.
+// d[k] = k < v ? s[k] : 0 for k in [lo, hi), s and d 16-byte aligned at 0: one
+// tile of kSteps steps of kCopyBlock threads x 8 elements, in 2-byte units
+// (bf16, or the halves of fp32 words for a plain copy).  The source window ends
+// with the last whole valid unit and the destination's with the last whole
+// unit, so a full and a short tile are the same loads and stores: units past
+// the valid ones read zero, units past the tile are dropped.  Only the lanes
+// of the units that are cut go element by element.
+template <int kSteps>
+__device__ __forceinline__ void seg_copy_aligned(const uint16_t* __restrict__ s, uint16_t* __restrict__ d, int64_t lo,
+                                                 int64_t hi, int64_t v) {
+    const int n = int(hi - lo), nv = clamp_to(v - lo, n);
+    const Window in = window(s + lo, uint32_t(nv / kVec) * 16);
+    const Window out = window(d + lo, uint32_t(n / kVec) * 16);
+    const bool cut = ((nv | n) & (kVec - 1)) != 0;
+    u32x4 x[kSteps];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) x[u] = ld16(in, (u * kCopyBlock + threadIdx.x) * 16);
+    if (!cut) {
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) st16(out, (u * kCopyBlock + threadIdx.x) * 16, x[u]);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        const int i = u * kCopyBlock + threadIdx.x;
+        const bool mine = (i == nv / kVec && (nv & (kVec - 1))) || (i == n / kVec && (n & (kVec - 1)));
+        st16(out, mine ? ~0u : uint32_t(i) * 16, x[u]);          // past the window: dropped
+        if (mine) copy_elements<kVec>(s, d, lo + i * kVec, v, hi, [](uint16_t x) { return x; });
+    }
+}
+
+// The same from and to any address (a dense bucket, A < 8, a view of flat
+// storage, or a destination off the 128-byte lines).  The stores follow d's
+// lines, so that no line is written in parts by two waves (which write-through
+// stores would send to memory in parts), and each 16-byte store is fed with
+// one load from any 2-byte address: such a load costs little more than an
+// aligned one (a plain copy of 1.7 GB: 517 us against 511; stores off the grid
+// as well: 555).  A tile stores the lines that start in [lo, hi); its last one
+// may run past hi into the next tile's elements (up to the segment's end e),
+// and the next tile starts with the line after it.  The segment's first
+// elements before its first line (in its first tile) and units cut by v or e
+// are written element by element.
 template <int kSteps>
 __device__ __forceinline__ void seg_copy_any(const uint16_t* __restrict__ s, uint16_t* __restrict__ d, int64_t lo,
                                              int64_t hi, int64_t v, int64_t e) {
-    const int64_t h = (8 - int64_t((reinterpret_cast<uintptr_t>(d + lo) >> 1) & 7)) & 7;
-    const int64_t a = lo + h;                          // the first grid point at or after lo
+    constexpr int kUnits = kSteps * kCopyBlock;
+    constexpr int kLine = 64;                          // elements
+    const int h = (kLine - (int(reinterpret_cast<uintptr_t>(d + lo) >> 1) & (kLine - 1))) & (kLine - 1);
+    const int64_t a = lo + h;                          // the first line at or after lo
     const int t = threadIdx.x;
-    if (lo == 0 && t < 8) {                            // the segment's elements before the grid
-        const int64_t k = t;
-        if (k < min(a, hi)) d[k] = k < v ? s[k] : uint16_t(0);
-    }
-    const int64_t nu = hi > a ? (hi - a + kVec - 1) / kVec : 0;   // grid units starting in [a, hi)
-    uint4 x[kSteps];
-#if FSDP_ANY_NEIGHBOUR
-    // Unit i reads source bytes [s + a + 16 i, + 16): offset r into its aligned
-    // block, the same r for every unit.  For r != 0 it also needs the next
-    // block, which is the block of unit i + 1, loaded by the next lane; that
-    // block is taken from the next lane, so each block is loaded once.  Lane 63
-    // of a wave, and a lane whose next unit is not loaded, load it themselves
-    // (it holds bytes of the unit's own range, as in ld16_any).
-    const uint32_t r = uint32_t(reinterpret_cast<uintptr_t>(s + a)) & 15u;
-    const bool last_lane = (t & 63) == 63;
-    u32x4 b0[kSteps], b1[kSteps];
-    bool ok[kSteps], own[kSteps];
+    const auto same = [](uint16_t x) { return x; };
+    if (lo == 0 && t < h) copy_elements<1>(s, d, t, v, min(a, hi), same);
+    // units from a on: the tile's, those read whole, and the whole ones of zeros
+    const int nu = clamp_to((hi - a + kLine - 1) / kLine * (kLine / kVec), kUnits);
+    const int whole = clamp_to((min(v, e) - a) >> 3, nu);
+    const int zero_from = clamp_to((v - a + kVec - 1) >> 3, nu), zero_to = clamp_to((e - a) >> 3, nu);
+    const Window out = window(d + a, uint32_t(nu) * 16);
+    const char* const from = as_global(reinterpret_cast<const char*>(s + a));
+    u32x4 x[kSteps];
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
-        const int64_t i = int64_t(u) * kCopyBlock + t;
-        const int64_t g = a + i * kVec;
-        ok[u] = i < nu && g + kVec <= v && g + kVec <= e;
-        const bool next_ok = i + 1 < nu && g + 2 * kVec <= v && g + 2 * kVec <= e;
-        own[u] = r != 0 && (last_lane || !next_ok);
-        const u32x4* q = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(s + g) - r);
-        if (ok[u]) b0[u] = ld_block(q);
-        if (ok[u] && own[u]) b1[u] = ld_block(q + 1);
+        const int i = u * kCopyBlock + t;
+        x[u] = u32x4{0, 0, 0, 0};
+        if (i < whole) x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any2*>(from + uint32_t(i) * 16));
     }
-    if (r == 0) {
-#pragma unroll
-        for (int u = 0; u < kSteps; ++u) x[u] = make_uint4(b0[u].x, b0[u].y, b0[u].z, b0[u].w);
-    } else {
-#pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const u32x4 n = next_lane(b0[u]);
-            if (ok[u]) x[u] = join16(b0[u], own[u] ? b1[u] : n, r);
-        }
-    }
-#else
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
-        const int64_t i = int64_t(u) * kCopyBlock + t;
-        const int64_t g = a + i * kVec;
-        if (i < nu && g + kVec <= v && g + kVec <= e) x[u] = ld16_any(s + g);
-    }
-#endif
-#pragma unroll
-    for (int u = 0; u < kSteps; ++u) {
-        const int64_t i = int64_t(u) * kCopyBlock + t;
-        const int64_t g = a + i * kVec;
-        if (i >= nu) continue;
-        if (g + kVec <= e) {
-            if (g + kVec <= v) st16(d + g, x[u]);
-            else if (g >= v) st16(d + g, make_uint4(0, 0, 0, 0));
-            else for (int k = 0; k < kVec; ++k) d[g + k] = g + k < v ? s[g + k] : uint16_t(0);
-        } else {                                       // the segment's last unit, cut by e
-            for (int64_t k = g; k < e; ++k) d[k] = k < v ? s[k] : uint16_t(0);
-        }
+        const int i = u * kCopyBlock + t;
+        const bool unit = i < whole || (i >= zero_from && i < zero_to);
+        st16(out, unit ? uint32_t(i) * 16 : ~0u, x[u]);          // past the window: dropped
+        if (!unit && i < nu) copy_elements<kVec>(s, d, a + int64_t(i) * kVec, v, e, same);
     }
 }
 
-// kAny: the launch has segments off the 16-byte grid, which take
-// seg_copy_any; without it such a tile is copied element by element (the
-// host picks kAny only when some segment needs it, so that the aligned
-// kernels keep their own code).
+// kAny: the launch has segments that start off the 16-byte grid or are written
+// off the 128-byte lines; those take seg_copy_any (the host picks kAny only
+// when there are some, so that the aligned kernels keep their own code).
 // (vs, e): the segment's valid elements and its end, for seg_copy_any, whose
-// units may run past hi.
+// lines may run past hi.
 template <int kSteps, bool kAny>
 __device__ __forceinline__ void seg_copy(const uint16_t* __restrict__ s, uint16_t* __restrict__ d, int64_t lo,
-                                         int64_t hi, int64_t v, bool vec, int64_t vs, int64_t e) {
-    constexpr int64_t kTile = int64_t(kCopyBlock) * kVec * kSteps;
+                                         int64_t hi, int64_t v, int64_t vs, int64_t e) {
     if constexpr (kAny) {
-        if (!vec) {
+        if (!is_aligned16(s) || !on_line(d)) {
             seg_copy_any<kSteps>(s, d, lo, hi, vs, e);
             return;
         }
     }
-    if (vec && hi - lo == kTile && (hi <= v || lo >= v)) {
-        const Window out = window(d + lo, kTile * 2);
-        if (hi <= v) {
-            const Window in = window(s + lo, kTile * 2);
-            u32x4 x[kSteps];
-#pragma unroll
-            for (int u = 0; u < kSteps; ++u) x[u] = ld16(in, (u * kCopyBlock + threadIdx.x) * 16);
-#pragma unroll
-            for (int u = 0; u < kSteps; ++u) st16(out, (u * kCopyBlock + threadIdx.x) * 16, x[u]);
-        } else {
-#pragma unroll
-            for (int u = 0; u < kSteps; ++u) st16(out, (u * kCopyBlock + threadIdx.x) * 16, u32x4{0, 0, 0, 0});
-        }
-        return;
-    }
-    for (int u = 0; u < kSteps; ++u) {
-        const int64_t g = lo + (int64_t(u) * kCopyBlock + threadIdx.x) * kVec;
-        if (g >= hi) break;
-        if (vec && g + kVec <= hi && (g + kVec <= v || g >= v)) {
-            st16(d + g, g < v ? ld16(s + g) : make_uint4(0, 0, 0, 0));
-            continue;
-        }
-        for (int e = 0; e < kVec; ++e) {
-            const int64_t k = g + e;
-            if (k >= hi) break;
-            d[k] = k < v ? s[k] : uint16_t(0);
-        }
-    }
+    seg_copy_aligned<kSteps>(s, d, lo, hi, v);
 }
 
 // As seg_copy, but 16-bit elements (bf16 or fp16, kFrom) in and their exact
-// fp32 values out.  Each thread handles 4 elements per sub-step (8 bytes in,
-// 16 bytes out), so that every load and store instruction of a wave covers
-// one contiguous run.
+// fp32 values out, from and to any element-aligned address: with s and d on
+// the 16-byte grid through windows, otherwise from where they are.  Each
+// thread handles 4 elements per sub-step (8 bytes in, 16 bytes out), so that
+// every load and store instruction of a wave covers one contiguous run.
 template <int kSteps, int kFrom>
 __device__ __forceinline__ void seg_widen(const uint16_t* __restrict__ s, float* __restrict__ d, int64_t lo,
-                                          int64_t hi, int64_t v, bool vec) {
-    constexpr int kSub = kSteps;
-    constexpr int64_t kTile = int64_t(kWidenBlock) * 4 * kSub;
-    if (vec && hi - lo == kTile && (hi <= v || lo >= v)) {
-        const Window out = window(d + lo, kTile * 4);
-        if (hi <= v) {
-            const Window in = window(s + lo, kTile * 2);
-            u32x2 x[kSub];
+                                          int64_t hi, int64_t v) {
+    const int n = int(hi - lo), nv = clamp_to(v - lo, n);
+    const bool direct = is_aligned16(s) && is_aligned16(d);
+    const char* const from = as_global(reinterpret_cast<const char*>(s + lo));
+    char* const to = as_global(reinterpret_cast<char*>(d + lo));
+    const auto cast = [](uint16_t x) { return widen_lo<kFrom>(x); };
+    u32x2 x[kSteps];
+    if (direct) {
+        const Window in = window(s + lo, uint32_t(nv / 4) * 8);
 #pragma unroll
-            for (int u = 0; u < kSub; ++u) x[u] = ld8(in, (u * kWidenBlock + threadIdx.x) * 8);
+        for (int u = 0; u < kSteps; ++u) x[u] = ld8(in, (u * kWidenBlock + threadIdx.x) * 8);
+    } else {
 #pragma unroll
-            for (int u = 0; u < kSub; ++u)
-                st16(out, (u * kWidenBlock + threadIdx.x) * 16,
-                     f32x4{widen_lo<kFrom>(x[u].x), widen_hi<kFrom>(x[u].x), widen_lo<kFrom>(x[u].y), widen_hi<kFrom>(x[u].y)});
-        } else {
-#pragma unroll
-            for (int u = 0; u < kSub; ++u) st16(out, (u * kWidenBlock + threadIdx.x) * 16, f32x4{0.f, 0.f, 0.f, 0.f});
+        for (int u = 0; u < kSteps; ++u) {
+            const int i = u * kWidenBlock + threadIdx.x;
+            x[u] = u32x2{0, 0};
+            if (i < nv / 4) x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any2*>(from + uint32_t(i) * 8));
         }
-        return;
     }
-    for (int u = 0; u < kSub; ++u) {
-        const int64_t g = lo + (int64_t(u) * kWidenBlock + threadIdx.x) * 4;
-        if (g >= hi) break;
-        if (vec && g + 4 <= hi && (g + 4 <= v || g >= v)) {
-            const uint2 x = g < v ? ld8(s + g) : make_uint2(0, 0);
-            st16f(d + g, make_float4(widen_lo<kFrom>(x.x), widen_hi<kFrom>(x.x),
-                                      widen_lo<kFrom>(x.y), widen_hi<kFrom>(x.y)));
-            continue;
+    const Window out = window(d + lo, uint32_t(n / 4) * 16);
+    const bool cut = ((nv | n) & 3) != 0;
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        const int i = u * kWidenBlock + threadIdx.x;
+        const f32x4 y = {widen_lo<kFrom>(x[u].x), widen_hi<kFrom>(x[u].x), widen_lo<kFrom>(x[u].y), widen_hi<kFrom>(x[u].y)};
+        const bool mine = cut && ((i == nv / 4 && (nv & 3)) || (i == n / 4 && (n & 3)));
+        if (direct) {
+            st16(out, mine ? ~0u : uint32_t(i) * 16, y);
+        } else if (!mine && i < n / 4) {
+            __builtin_nontemporal_store(y, reinterpret_cast<f32x4_any4*>(to + uint32_t(i) * 16));
         }
-        for (int e = 0; e < 4; ++e) {
-            const int64_t k = g + e;
-            if (k >= hi) break;
-            d[k] = k < v ? widen_lo<kFrom>(s[k]) : 0.f;
-        }
+        if (mine) copy_elements<4>(s, d, lo + i * 4, v, hi, cast);
     }
 }
 
@@ -538,12 +528,9 @@ __device__ __forceinline__ int64_t from_lane(int64_t v, int p) {
     const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u >> 32)), p));
     return int64_t((uint64_t(hi) << 32) | lo);
 }
-// A pointer into device memory: the round trip through the global address
-// space keeps its accesses global rather than flat instructions.
 template <typename T>
 __device__ __forceinline__ T* from_lane(T* v, int p) {
-    typedef T __attribute__((address_space(1))) Global;
-    return (T*)(Global*)(from_lane(reinterpret_cast<int64_t>(v), p));
+    return as_global(reinterpret_cast<T*>(from_lane(reinterpret_cast<int64_t>(v), p)));
 }
 
 // The pack's lane-held table: lane l holds parameter l's entries.
@@ -814,21 +801,19 @@ Divider divider(uint32_t d) {
 #define FSDP_COPY_WAVES 5
 #endif
 constexpr int kCopyWaves = FSDP_COPY_WAVES;       // resident waves per SIMD
-constexpr int kCopyAnyWaves = kCopyWaves + 1;     // where units are joined from two blocks (below)
+#ifndef FSDP_COPY_ANY_WAVES
+#define FSDP_COPY_ANY_WAVES 6
+#endif
+constexpr int kCopyAnyWaves = FSDP_COPY_ANY_WAVES;   // ... where some segment is off the grid
 // The widening pack has half the bytes in flight per wave: no cap.
 template <int kWiden, bool kAny> constexpr int kPackMinWaves = kWiden != kF32 ? 4 : kAny ? kCopyAnyWaves : kCopyWaves;
 template <int kWiden, bool kAny> constexpr int kPackMaxWaves = kWiden != kF32 ? 8 : kAny ? kCopyAnyWaves : kCopyWaves;
 
-constexpr int kPivots = 16;
-constexpr int kPerPivot = 4;
-static_assert(kPivots * kPerPivot >= PMAX, "the pivots cover every parameter");
 struct CopyTiles {
     uint32_t ntiles;               // W * per_chunk
     uint32_t per_chunk;            // tiles of one chunk
     Divider by_chunk;              // n / per_chunk
-    uint32_t pivot[kPivots];       // first tile (in a chunk) of parameter k, or of 4k if `deep`; UINT_MAX past the last
-    uint32_t deep;                 // more than kPivots parameters
-    uint32_t start[PMAX];          // first tile of every parameter; UINT_MAX past the last
+    TileTable table;               // of one chunk's tiles
 };
 
 // One parameter of a W-way copy, in 2-byte units (or 16-bit elements where
@@ -850,6 +835,7 @@ struct alignas(32) CopyParam {
 __device__ __forceinline__ CopyParam load_param(const CopyParam* params, int p) {
     CopyParam q = params[p];
     asm volatile("" : "+s"(q.data), "+s"(q.off), "+s"(q.seg), "+s"(q.elems));
+    q.data = as_global(q.data);
     return q;
 }
 
@@ -860,29 +846,10 @@ struct CopyPlace {
     __device__ __forceinline__ CopyPlace(const CopyTiles& c, uint32_t step) {
         const uint32_t t = copy_tile(step, c.ntiles);
         const uint32_t i = c.by_chunk.quotient(t);
-        const uint32_t r = t - i * c.per_chunk;
-        int k = -1;                                  // the last pivot at or before r
-        uint32_t first = 0;
-#pragma unroll
-        for (int e = 0; e < kPivots; ++e) {
-            const bool in = c.pivot[e] <= r;
-            k = in ? e : k;
-            first = in ? c.pivot[e] : first;
-        }
-        if (c.deep) {
-            k *= kPerPivot;
-            const int base = k;
-#pragma unroll
-            for (int e = 0; e < kPerPivot; ++e) {
-                const uint32_t f = c.start[base + e];
-                const bool in = f <= r;
-                k = in ? base + e : k;
-                first = in ? f : first;
-            }
-        }
+        const TilePlace at(c.table, t - i * c.per_chunk);
         chunk = int(i);
-        param = k;
-        tile = r - first;
+        param = at.param;
+        tile = at.tile;
     }
 };
 
@@ -912,7 +879,7 @@ ag_unpack_kernel(const UnpackArgs<Chunks> a) {
         if (lo >= hi) continue;
         const uint16_t* s = reinterpret_cast<const uint16_t*>(a.src.at(i)) + q.off;
         uint16_t* d = q.data + int64_t(i) * q.seg;
-        seg_copy<kCopySteps, kAny>(s, d, lo, hi, hi, is_aligned16(s) && is_aligned16(d), v, v);
+        seg_copy<kCopySteps, kAny>(s, d, lo, hi, hi, v, v);
     } while (step < a.tiles.ntiles);
 }
 
@@ -946,331 +913,290 @@ rs_pack_kernel(const RsPackArgs<Chunks> a) {
         const uint16_t* s = q.data + int64_t(j) * q.seg;
         if constexpr (kWiden != kF32) {
             float* d = reinterpret_cast<float*>(a.dst.at(j)) + q.off;
-            seg_widen<kWidenSteps, kWiden>(s, d, lo, hi, v, is_aligned16(s) && is_aligned16(d));
+            seg_widen<kWidenSteps, kWiden>(s, d, lo, hi, v);
         } else {
             uint16_t* d = reinterpret_cast<uint16_t*>(a.dst.at(j)) + q.off;
-            seg_copy<kCopySteps, kAny>(s, d, lo, hi, v, is_aligned16(s) && is_aligned16(d), v, region);
+            seg_copy<kCopySteps, kAny>(s, d, lo, hi, v, v, region);
         }
     } while (step < a.tiles.ntiles);
 }
 
 // ------------------------------------------------------------------ rs_reduce
 
+// One parameter of a reduction: one 32-byte scalar load.
+struct alignas(32) ReduceParam {
+    float* dst;
+    int64_t off;                 // off_p
+    int64_t valid;               // n_{p,rank} * inner_p
+};
+
 template <class Chunks>
 struct ReduceArgs {
-    float* dst[PMAX];
-    int64_t off[PMAX];
-    int64_t valid[PMAX];         // n_{p,rank} * inner_p
-    int32_t tile_start[PMAX];    // first tile of parameter p; INT_MAX past the last parameter
-    Chunks src;                  // received chunks, one per source rank
+    uint32_t ntiles;
     int32_t world;
-    int32_t nparams;
-    int32_t ntiles;
+    TileTable table;
+    Chunks src;                  // received chunks, one per source rank
+    ReduceParam param[PMAX];
 };
 
-__device__ __forceinline__ void add8(float (&acc)[8], uint4 x) {
-    acc[0] += bf16_lo(x.x); acc[1] += bf16_hi(x.x);
-    acc[2] += bf16_lo(x.y); acc[3] += bf16_hi(x.y);
-    acc[4] += bf16_lo(x.z); acc[5] += bf16_hi(x.z);
-    acc[6] += bf16_lo(x.w); acc[7] += bf16_hi(x.w);
-}
-
-__device__ __forceinline__ void init8(float (&acc)[8], uint4 x) {
-    acc[0] = bf16_lo(x.x); acc[1] = bf16_hi(x.x);
-    acc[2] = bf16_lo(x.y); acc[3] = bf16_hi(x.y);
-    acc[4] = bf16_lo(x.z); acc[5] = bf16_hi(x.z);
-    acc[6] = bf16_lo(x.w); acc[7] = bf16_hi(x.w);
-}
-
-// One thread's 8 values of a tile row (kB * 8 elements, kB threads) of one
-// source, as loaded.  bf16 sources: elements [8t, 8t+8) of the row, one
-// 16-byte load.  fp32 sources: elements [4t, 4t+4) and [4kB + 4t, 4kB + 4t + 4),
-// two 16-byte loads that each cover one contiguous run across the wave.
-// Addresses are a wave-uniform row pointer plus a 32-bit byte offset.
-template <typename T, int kB> struct Raw8;
-template <int kB> struct Raw8<uint16_t, kB> {
-    uint4 x;
-    __device__ __forceinline__ static uint32_t pos(uint32_t t, int e) { return t * 8 + e; }
-    __device__ __forceinline__ void load(const uint16_t* row, uint32_t t) { x = ld16(row + t * 8); }
-    __device__ __forceinline__ void load_any(const uint16_t* row, uint32_t t) { x = ld16_any(row + t * 8); }
-    __device__ __forceinline__ void init(float (&acc)[8]) const { init8(acc, x); }
-    __device__ __forceinline__ void add(float (&acc)[8]) const { add8(acc, x); }
+// The 16 bytes a lane loads from one source: kPer elements, added to as many
+// fp32 sums.
+template <typename T> struct Unit;
+template <> struct Unit<uint16_t> {
+    static constexpr int kPer = 8;
+    __device__ __forceinline__ static void add(float (&acc)[8], const u32x4& x) {
+        acc[0] += bf16_lo(x.x); acc[1] += bf16_hi(x.x);
+        acc[2] += bf16_lo(x.y); acc[3] += bf16_hi(x.y);
+        acc[4] += bf16_lo(x.z); acc[5] += bf16_hi(x.z);
+        acc[6] += bf16_lo(x.w); acc[7] += bf16_hi(x.w);
+    }
+    __device__ __forceinline__ static float widen(uint16_t x) { return bf16_lo(x); }
 };
-template <int kB> struct Raw8<_Float16, kB> {
-    uint4 x;
-    __device__ __forceinline__ static uint32_t pos(uint32_t t, int e) { return t * 8 + e; }
-    __device__ __forceinline__ void load(const _Float16* row, uint32_t t) { x = ld16(row + t * 8); }
-    __device__ __forceinline__ void load_any(const _Float16* row, uint32_t t) { x = ld16_any(row + t * 8); }
-    __device__ __forceinline__ void init(float (&acc)[8]) const {
-        acc[0] = f16_lo(x.x); acc[1] = f16_hi(x.x); acc[2] = f16_lo(x.y); acc[3] = f16_hi(x.y);
-        acc[4] = f16_lo(x.z); acc[5] = f16_hi(x.z); acc[6] = f16_lo(x.w); acc[7] = f16_hi(x.w);
+template <> struct Unit<_Float16> {
+    static constexpr int kPer = 8;
+    __device__ __forceinline__ static void add(float (&acc)[8], const u32x4& x) {
+        acc[0] += f16_lo(x.x); acc[1] += f16_hi(x.x);
+        acc[2] += f16_lo(x.y); acc[3] += f16_hi(x.y);
+        acc[4] += f16_lo(x.z); acc[5] += f16_hi(x.z);
+        acc[6] += f16_lo(x.w); acc[7] += f16_hi(x.w);
     }
-    __device__ __forceinline__ void add(float (&acc)[8]) const {
-        acc[0] += f16_lo(x.x); acc[1] += f16_hi(x.x); acc[2] += f16_lo(x.y); acc[3] += f16_hi(x.y);
-        acc[4] += f16_lo(x.z); acc[5] += f16_hi(x.z); acc[6] += f16_lo(x.w); acc[7] += f16_hi(x.w);
-    }
+    __device__ __forceinline__ static float widen(_Float16 x) { return static_cast<float>(x); }
 };
-template <int kB> struct Raw8<float, kB> {
-    float4 a, b;
-    __device__ __forceinline__ static uint32_t pos(uint32_t t, int e) {
-        return e < 4 ? t * 4 + e : uint32_t(kB) * 4 + t * 4 + (e - 4);
+template <> struct Unit<float> {
+    static constexpr int kPer = 4;
+    __device__ __forceinline__ static void add(float (&acc)[4], const u32x4& x) {
+        acc[0] += __uint_as_float(x.x); acc[1] += __uint_as_float(x.y);
+        acc[2] += __uint_as_float(x.z); acc[3] += __uint_as_float(x.w);
     }
-    __device__ __forceinline__ void load(const float* row, uint32_t t) {
-        a = ld16f(row + t * 4);
-        b = ld16f(row + uint32_t(kB) * 4 + t * 4);
-    }
-    __device__ __forceinline__ void load_any(const float* row, uint32_t t) {
-        const uint4 u = ld16_any(row + t * 4);
-        const uint4 w = ld16_any(row + uint32_t(kB) * 4 + t * 4);
-        a = make_float4(__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w));
-        b = make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w));
-    }
-    __device__ __forceinline__ void init(float (&acc)[8]) const {
-        acc[0] = a.x; acc[1] = a.y; acc[2] = a.z; acc[3] = a.w;
-        acc[4] = b.x; acc[5] = b.y; acc[6] = b.z; acc[7] = b.w;
-    }
-    __device__ __forceinline__ void add(float (&acc)[8]) const {
-        acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
-        acc[4] += b.x; acc[5] += b.y; acc[6] += b.z; acc[7] += b.w;
-    }
+    __device__ __forceinline__ static float widen(float x) { return x; }
 };
 
-// Store the 8 averages of thread t at the positions Raw8<T, kB>::pos gives.
-template <typename T, int kB>
-__device__ __forceinline__ void store_avg8(float* row, uint32_t t, const float (&acc)[8], float wf) {
-    const float4 lo = make_float4(acc[0] / wf, acc[1] / wf, acc[2] / wf, acc[3] / wf);
-    const float4 hi = make_float4(acc[4] / wf, acc[5] / wf, acc[6] / wf, acc[7] / wf);
-    st16f(row + Raw8<T, kB>::pos(t, 0), lo);
-    st16f(row + Raw8<T, kB>::pos(t, 4), hi);
+// A lane's 16-byte unit of one source: through a window of the tile's whole
+// units (a lane past them reads zero), or (not kDirect) from any
+// element-aligned address, `in` saying whether the lane has a unit.
+template <bool kDirect, typename T>
+__device__ __forceinline__ u32x4 load_unit(const char* tile, uint32_t unit_bytes, uint32_t lane_byte, bool in) {
+    if constexpr (kDirect) return ld16(window(tile, unit_bytes), lane_byte);
+    typedef typename std::conditional<sizeof(T) == 2, u32x4_any2, u32x4_any4>::type Any;
+    return in ? __builtin_nontemporal_load(reinterpret_cast<const Any*>(as_global(tile) + lane_byte)) : u32x4{0, 0, 0, 0};
 }
 
-// Typed pointer to the tile of source i: through the chunk table, or as a
-// strided tile of one contiguous buffer.
-template <typename T>
-__device__ __forceinline__ const T* source(const TableChunks& c, int64_t off, int i) {
-    return reinterpret_cast<const T*>(c.at(i)) + off;
-}
-template <typename T>
-__device__ __forceinline__ const T* source(const StridedTile<T>& c, int64_t off, int i) {
-    return c.at(i) + off;
-}
-
-// Loads of sources i0 .. i0+kReduceBatch-1 (those below W unless kFull) of a
-// full tile; all are issued before any of them is used.  `off` is the tile's
-// element offset inside every chunk.  kAny: the sources are not 16-byte
-// aligned there (a dense bucket), so each 16 bytes come from ld16_any.
-template <bool kFull, bool kAny, typename T, int kB, class Src>
-__device__ __forceinline__ void load_sources(Raw8<T, kB> (&x)[kReduceBatch][kReduceSteps], const Src& src,
-                                             int64_t off, int i0, int W, uint32_t t) {
-    constexpr uint32_t kRow = uint32_t(kB) * kVec;
-#pragma unroll
-    for (int b = 0; b < kReduceBatch; ++b) {
-        if (kFull || i0 + b < W) {
-            const T* s = source<T>(src, off, i0 + b);
-#pragma unroll
-            for (int u = 0; u < kReduceSteps; ++u) {
-                if constexpr (kAny) x[b][u].load_any(s + u * kRow, t);
-                else x[b][u].load(s + u * kRow, t);
-            }
-        }
-    }
-}
-
-// A full tile of kReduceSteps rows.  The W sources of every output are added
-// in rank order 0..W-1, starting from source 0; the loads of kReduceBatch
-// sources are issued ahead of their adds.
-template <typename T, int kB, bool kAny, class Src>
-__device__ __forceinline__ void reduce_tile_vec(const Src& src, int64_t off, float* __restrict__ dtile,
-                                                int W, float wf) {
-    constexpr uint32_t kRow = uint32_t(kB) * kVec;
+// The sums of a tile's whole units: row r of lane t holds outputs [kPer u,
+// kPer u + kPer) with u = r * kB + t.  The W sources of every output are added
+// in rank order; the loads of kNB sources are issued before the first of them
+// is added.  A sum starts from -0, which leaves the first value as it is (its
+// sign of zero too).
+template <typename T, int kB, int kRows, int kNB, bool kDirect, class Chunks>
+__device__ __forceinline__ void sum_units(float (&acc)[kRows][Unit<T>::kPer], const Chunks& src, int W, int64_t byte,
+                                          uint32_t units) {
     const uint32_t t = threadIdx.x;
-    float acc[kReduceSteps][8];
-    Raw8<T, kB> x[kReduceBatch][kReduceSteps];
-    if (W >= kReduceBatch) load_sources<true, kAny>(x, src, off, 0, W, t);
-    else load_sources<false, kAny>(x, src, off, 0, W, t);
 #pragma unroll
-    for (int u = 0; u < kReduceSteps; ++u) x[0][u].init(acc[u]);
+    for (int r = 0; r < kRows; ++r)
 #pragma unroll
-    for (int b = 1; b < kReduceBatch; ++b)
-        if (b < W) {
+        for (int e = 0; e < Unit<T>::kPer; ++e) acc[r][e] = -0.f;
+    const char* at[kNB];
 #pragma unroll
-            for (int u = 0; u < kReduceSteps; ++u) x[b][u].add(acc[u]);
-        }
-    int i = kReduceBatch;
-    for (; i + kReduceBatch <= W; i += kReduceBatch) {
-        load_sources<true, kAny>(x, src, off, i, W, t);
+    for (int b = 0; b < kNB; ++b) at[b] = src.ahead(b, W) + byte;
+    u32x4 x[kNB][kRows];
+    int i = 0;
+    for (; i + kNB <= W; i += kNB) {
 #pragma unroll
-        for (int b = 0; b < kReduceBatch; ++b)
+        for (int b = 0; b < kNB; ++b)
 #pragma unroll
-            for (int u = 0; u < kReduceSteps; ++u) x[b][u].add(acc[u]);
+            for (int r = 0; r < kRows; ++r)
+                x[b][r] = load_unit<kDirect, T>(at[b], units * 16, (r * kB + t) * 16, r * kB + t < units);
+        // the next batch's addresses (from the chunk table) while these loads run
+#pragma unroll
+        for (int b = 0; b < kNB; ++b) at[b] = src.ahead(i + kNB + b, W) + byte;
+#pragma unroll
+        for (int b = 0; b < kNB; ++b)
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) Unit<T>::add(acc[r], x[b][r]);
     }
-    if (i < W) {
-        load_sources<false, kAny>(x, src, off, i, W, t);
 #pragma unroll
-        for (int b = 0; b < kReduceBatch; ++b)
-            if (i + b < W) {
+    for (int b = 0; b < kNB - 1; ++b)
+        if (i + b < W) {
 #pragma unroll
-                for (int u = 0; u < kReduceSteps; ++u) x[b][u].add(acc[u]);
+            for (int r = 0; r < kRows; ++r)
+                x[b][r] = load_unit<kDirect, T>(at[b], units * 16, (r * kB + t) * 16, r * kB + t < units);
+        }
+#pragma unroll
+    for (int b = 0; b < kNB - 1; ++b)
+        if (i + b < W) {
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) Unit<T>::add(acc[r], x[b][r]);
+        }
+}
+
+// One output, at element `at` of every chunk (the elements past a tile's
+// whole units).
+template <typename T, int kNB, class Chunks>
+__device__ __forceinline__ float sum_one(const Chunks& src, int W, int64_t at) {
+    float acc = -0.f;
+    for (int i = 0; i < W; i += kNB) {
+        T x[kNB];
+#pragma unroll
+        for (int b = 0; b < kNB; ++b) x[b] = reinterpret_cast<const T*>(src.at(min(i + b, W - 1)))[at];
+#pragma unroll
+        for (int b = 0; b < kNB; ++b) {
+            const float sum = acc + Unit<T>::widen(x[b]);
+            acc = i + b < W ? sum : acc;
+        }
+    }
+    return acc;
+}
+
+// The averages of a tile's whole units.  A lane holds 8 outputs of a 16-bit
+// wire: they pass through the wave's own part of LDS, so that every store
+// instruction writes one contiguous run (stored as two halves per lane, every
+// 128-byte line is written in two parts: 330 us instead of 285 on the 70B
+// block's shape).  No other wave reads it, so no barrier is needed: a wave's
+// LDS accesses stay in order.
+template <int kB, int kRows, bool kDirect, int kPer>
+__device__ __forceinline__ void store_units(float* tile, uint32_t units, const float (&acc)[kRows][kPer], float wf) {
+    __shared__ f32x4 stage[kPer == 8 ? kB * 2 : 1];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x & ~63u;
+    const uint32_t quads = units * (kPer / 4);       // 16-byte outputs of the tile
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        f32x4 out[kPer / 4];
+        if constexpr (kPer == 4) {
+            out[0] = f32x4{acc[r][0] / wf, acc[r][1] / wf, acc[r][2] / wf, acc[r][3] / wf};
+        } else {
+            f32x4* const mine = stage + wave * 2;
+            mine[lane * 2] = f32x4{acc[r][0] / wf, acc[r][1] / wf, acc[r][2] / wf, acc[r][3] / wf};
+            mine[lane * 2 + 1] = f32x4{acc[r][4] / wf, acc[r][5] / wf, acc[r][6] / wf, acc[r][7] / wf};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            out[0] = mine[lane];
+            out[1] = mine[64 + lane];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int h = 0; h < kPer / 4; ++h) {
+            const uint32_t q = (r * kB + wave) * (kPer / 4) + h * 64 + lane;
+            if constexpr (kDirect) {
+                st16(window(tile, quads * 16), q * 16, out[h]);
+            } else {
+                if (q < quads) __builtin_nontemporal_store(out[h], reinterpret_cast<f32x4_any4*>(tile + q * 4));
             }
-    }
-    if constexpr (sizeof(T) == 2) {
-        // Thread t holds outputs [8t, 8t + 8) of each row: staged through LDS
-        // so that every store instruction of a wave covers one contiguous run.
-        __shared__ float4 stage[kReduceSteps * kB * 2];
-#pragma unroll
-        for (int u = 0; u < kReduceSteps; ++u) {
-            stage[(u * kB + t) * 2] = make_float4(acc[u][0] / wf, acc[u][1] / wf, acc[u][2] / wf, acc[u][3] / wf);
-            stage[(u * kB + t) * 2 + 1] = make_float4(acc[u][4] / wf, acc[u][5] / wf, acc[u][6] / wf, acc[u][7] / wf);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kReduceSteps; ++u)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                st16f(dtile + u * kRow + (h * kB + t) * 4, stage[u * kB * 2 + h * kB + t]);
-        __syncthreads();
-        return;
-    }
-#pragma unroll
-    for (int u = 0; u < kReduceSteps; ++u) store_avg8<T, kB>(dtile + u * kRow, t, acc[u], wf);
-}
-
-__device__ __forceinline__ float widen(uint16_t x) { return bf16_lo(x); }
-__device__ __forceinline__ float widen(_Float16 x) { return static_cast<float>(x); }
-__device__ __forceinline__ float widen(float x) { return x; }
-
-// One thread's group of 8 outputs of one row whose group lies wholly inside
-// the shard (partial tiles): the same rank-ordered sum, loads issued
-// kReduceBatch sources ahead.
-template <typename T, int kB, bool kAny, class Src>
-__device__ __forceinline__ void reduce_group_vec(const Src& src, int64_t off, float* __restrict__ drow, int W,
-                                                 float wf, uint32_t t) {
-    float acc[8];
-    Raw8<T, kB> x[kReduceBatch];
-    for (int i = 0; i < W; i += kReduceBatch) {
-#pragma unroll
-        for (int b = 0; b < kReduceBatch; ++b)
-            if (i + b < W) {
-                if constexpr (kAny) x[b].load_any(source<T>(src, off, i + b), t);
-                else x[b].load(source<T>(src, off, i + b), t);
-            }
-#pragma unroll
-        for (int b = 0; b < kReduceBatch; ++b) {
-            if (i + b >= W) break;
-            if (i + b == 0) x[b].init(acc);
-            else x[b].add(acc);
         }
     }
-    store_avg8<T, kB>(drow, t, acc, wf);
 }
 
-// One output element at element offset `g` of every chunk (unaligned or
-// ragged parts), loads issued kReduceBatch sources ahead.
-template <typename T, class Src>
-__device__ __forceinline__ float reduce_one(const Src& src, int64_t g, int W, float wf) {
-    float acc = 0.f;
-    T x[kReduceBatch];
-    for (int i = 0; i < W; i += kReduceBatch) {
-#pragma unroll
-        for (int b = 0; b < kReduceBatch; ++b)
-            if (i + b < W) x[b] = source<T>(src, g, i + b)[0];
-#pragma unroll
-        for (int b = 0; b < kReduceBatch; ++b) {
-            if (i + b >= W) break;
-            acc = (i + b == 0) ? widen(x[b]) : acc + widen(x[b]);
-        }
+// A tile of a reduction: elements [first, first + n) of every chunk, n <= kElems.
+template <int kElems>
+struct ReduceSpot {
+    int64_t first;
+    uint32_t n;
+    float* out;
+    template <class Args>
+    __device__ __forceinline__ ReduceSpot(const Args& a, uint32_t step) {
+        const TilePlace at(a.table, step);
+        ReduceParam q = a.param[at.param];
+        asm volatile("" : "+s"(q.dst), "+s"(q.off), "+s"(q.valid));   // one load, here
+        const int64_t lo = int64_t(at.tile) * kElems;
+        const int64_t rest = q.valid - lo;
+        n = rest < kElems ? uint32_t(rest) : uint32_t(kElems);        // at least 1
+        first = q.off + lo;
+        out = as_global(q.dst) + lo;
     }
-    return acc / wf;
-}
+};
 
-// kB threads per workgroup, each owning kReduceSteps groups of 8 outputs: a
-// tile of kB * 8 * kReduceSteps outputs.  kAny: some parameter's sources are
-// off the 16-byte grid (the host picks it only then).  The parameter of each
-// tile and its fields come from lane-held tables.
-template <class Chunks, typename T, int kB, bool kAny>
-__global__ void __launch_bounds__(kB) rs_reduce_kernel(const ReduceArgs<Chunks> a) {
-    constexpr int64_t kRow = int64_t(kB) * kVec;
-    constexpr int64_t kTile = kRow * kReduceSteps;
-    const int l = table_lane();
-#if FSDP_LDS_TABLE
-    const int my_start = staged_entry(a.tile_start, a.nparams);
-#else
-    const int my_start = lane_index() < PMAX ? a.tile_start[l] : INT_MAX;
-#endif
-    const int64_t my_valid = a.valid[l], my_off = a.off[l];
-    float* const my_dst = a.dst[l];
+// What bounds the reduction is HBM: W reads for one fp32 write.  As in the
+// copies, the bytes in flight decide the rate: 16-32 KB of loads per CU stream
+// best, and more make it slower again, because the reads of many places (and
+// the few writes among them) then meet in the memory controllers.  So a
+// workgroup is one wave with one unit per lane, kNB sources are in flight
+// while the kNB before them are added, and the host picks kNB and the resident
+// waves per SIMD by the waves that the whole shard makes (ReduceForm).
+//
+// Every batch issues the same number of loads (a source past W, or a tile past
+// the last, has an empty window), so the wait for a batch never waits for the
+// next one; the loads of a workgroup's next tile are issued before the current
+// one is finished.
+//
+// kAny: some parameter's sources or outputs are off the 16-byte grid (the
+// host picks it only then).  Such tiles load and store at any element, and a
+// batch is added before the next one is loaded.
+template <class Chunks, typename T, int kNB, int kMaxWaves, bool kAny>
+__global__ void __launch_bounds__(kReduceBlock)
+__attribute__((amdgpu_waves_per_eu(kMaxWaves < 8 ? kMaxWaves : kNB > 2 ? 4 : 8, kMaxWaves)))
+rs_reduce_kernel(const ReduceArgs<Chunks> a) {
+    constexpr int kPer = Unit<T>::kPer;
+    typedef ReduceSpot<kReduceBlock * kPer> Spot;
+    const uint32_t t = threadIdx.x;
     const int W = a.world;
     const float wf = float(W);
-    const uint32_t t = threadIdx.x;
-    for (int64_t step = blockIdx.x; step < a.ntiles; step += gridDim.x) {
-        const int tile = int(step);
-        const int p = param_of_tile(my_start, tile);
-        const int64_t v = from_lane(my_valid, p);
-        const int64_t lo = int64_t(tile - from_lane(my_start, p)) * kTile;
-        const int64_t off = from_lane(my_off, p);
-        float* __restrict__ d0 = from_lane(my_dst, p);
-        // Outputs are stored 16 bytes at a time when d0 is 16-byte aligned
-        // and the sources loaded 16 bytes at a time: directly when they are
-        // 16-byte aligned, through ld16_any otherwise (kAny only).
-        bool vec, svec;
-        if constexpr (kAny) {
-            vec = is_aligned16(d0);
-            svec = a.src.aligned() && ((off * int64_t(sizeof(T))) & 15) == 0;
-        } else {
-            vec = is_aligned16(d0) && a.src.aligned() && ((off * int64_t(sizeof(T))) & 15) == 0;
-            svec = true;
-        }
-        if (vec && lo + kTile <= v) {
-            if (std::is_same<Chunks, ContigChunks>::value) {
-                const ContigChunks& c = reinterpret_cast<const ContigChunks&>(a.src);
-                const StridedTile<T> st{reinterpret_cast<const T*>(c.base) + off + lo,
-                                        c.stride / int64_t(sizeof(T))};
-                if (!kAny || svec) reduce_tile_vec<T, kB, false>(st, 0, d0 + lo, W, wf);
-                else reduce_tile_vec<T, kB, kAny>(st, 0, d0 + lo, W, wf);
+    uint32_t step = blockIdx.x;
+    if constexpr (kAny) {
+        do {
+            const Spot s(a, step);
+            step += gridDim.x;
+            const uint32_t units = s.n / kPer;
+            const int64_t byte = s.first * int64_t(sizeof(T));
+            float acc[1][kPer];
+            if (a.src.aligned() && (byte & 15) == 0 && is_aligned16(s.out)) {
+                sum_units<T, kReduceBlock, 1, kNB, true>(acc, a.src, W, byte, units);
+                store_units<kReduceBlock, 1, true>(s.out, units, acc, wf);
             } else {
-                const TableChunks& c = reinterpret_cast<const TableChunks&>(a.src);
-                if (!kAny || svec) reduce_tile_vec<T, kB, false>(c, off + lo, d0 + lo, W, wf);
-                else reduce_tile_vec<T, kB, kAny>(c, off + lo, d0 + lo, W, wf);
+                sum_units<T, kReduceBlock, 1, kNB, false>(acc, a.src, W, byte, units);
+                store_units<kReduceBlock, 1, false>(s.out, units, acc, wf);
             }
-            continue;
-        }
-        // partial tile: row by row; a thread's group vectorised when all of it is in range
-        for (int u = 0; u < kReduceSteps; ++u) {
-            const int64_t row = lo + u * kRow;
-            if (row >= v) break;
-            if (vec && row + Raw8<T, kB>::pos(t, 7) < v) {
-                if (std::is_same<Chunks, ContigChunks>::value) {
-                    const ContigChunks& c = reinterpret_cast<const ContigChunks&>(a.src);
-                    const StridedTile<T> st{reinterpret_cast<const T*>(c.base) + off + row,
-                                            c.stride / int64_t(sizeof(T))};
-                    if (!kAny || svec) reduce_group_vec<T, kB, false>(st, 0, d0 + row, W, wf, t);
-                    else reduce_group_vec<T, kB, kAny>(st, 0, d0 + row, W, wf, t);
-                } else {
-                    const TableChunks& c = reinterpret_cast<const TableChunks&>(a.src);
-                    if (!kAny || svec) reduce_group_vec<T, kB, false>(c, off + row, d0 + row, W, wf, t);
-                    else reduce_group_vec<T, kB, kAny>(c, off + row, d0 + row, W, wf, t);
-                }
-                continue;
-            }
-            for (int e = 0; e < kVec; ++e) {
-                const int64_t g = row + Raw8<T, kB>::pos(t, e);
-                if (g >= v) continue;
-                if (std::is_same<Chunks, ContigChunks>::value) {
-                    const ContigChunks& c = reinterpret_cast<const ContigChunks&>(a.src);
-                    const StridedTile<T> st{reinterpret_cast<const T*>(c.base), c.stride / int64_t(sizeof(T))};
-                    d0[g] = reduce_one<T>(st, off + g, W, wf);
-                } else {
-                    d0[g] = reduce_one<T>(reinterpret_cast<const TableChunks&>(a.src), off + g, W, wf);
-                }
-            }
-        }
+            const uint32_t k = units * kPer + t;                  // fewer than kPer elements are left
+            if (k < s.n) s.out[k] = sum_one<T, 4>(a.src, W, s.first + k) / wf;
+        } while (step < a.ntiles);
+        return;
     }
+    Spot next(a, step);                         // the tile whose loads are issued
+    int i = 0;                                  // its next source
+    u32x4 x[2][kNB];
+    const auto load = [&](u32x4 (&y)[kNB]) {
+        const uint32_t bytes = step < a.ntiles ? next.n / kPer * 16 : 0;
+#pragma unroll
+        for (int b = 0; b < kNB; ++b)
+            y[b] = ld16(window(a.src.ahead(i + b, W) + next.first * int64_t(sizeof(T)), i + b < W ? bytes : 0), t * 16);
+        i += kNB;
+    };
+    load(x[0]);
+    do {
+        const Spot s = next;
+        float acc[1][kPer];
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) acc[0][e] = -0.f;
+        const auto add = [&](const u32x4 (&y)[kNB], int sources) {
+#pragma unroll
+            for (int b = 0; b < kNB; ++b)
+                if (b < sources) Unit<T>::add(acc[0], y[b]);
+        };
+        int j = 0;
+        for (; j + 2 * kNB < W; j += 2 * kNB) {
+            load(x[1]);
+            __builtin_amdgcn_sched_barrier(0);  // the next batch's loads stay before this one's adds
+            add(x[0], kNB);
+            load(x[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            add(x[1], kNB);
+        }
+        load(x[1]);
+        step += gridDim.x;
+        if (step < a.ntiles) next = Spot(a, step);
+        i = 0;
+        __builtin_amdgcn_sched_barrier(0);
+        add(x[0], W - j);
+        load(x[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        add(x[1], W - j - kNB);
+        const uint32_t units = s.n / kPer;
+        store_units<kReduceBlock, 1, true>(s.out, units, acc, wf);
+        const uint32_t k = units * kPer + t;                      // fewer than kPer elements are left
+        if (k < s.n) s.out[k] = sum_one<T, 4>(a.src, W, s.first + k) / wf;
+    } while (step < a.ntiles);
 }
 
 // ------------------------------------------------------------------ host side
 
-// Below this many full-size reduce tiles per CU, the reduce uses half-size tiles.
-constexpr int kSmallShardTilesPerCU = 4;
 // From this many big pack tiles per CU up, a single-chunk pack uses them.
 constexpr int kPackBigTilesPerCU = 4;
 
@@ -1483,29 +1409,42 @@ fsdp_status do_ag_pack_one(const fsdp_plan* h, int32_t rank, const float* const*
     return do_ag_pack(*pl, rank, shards, wire, OneChunk{static_cast<char*>(send_chunk)}, 1, outs, stream);
 }
 
+// The rest of a tile table, once every parameter has its start.
+void finish_table(const Plan& pl, TileTable* c) {
+    for (int p = pl.nparams; p < PMAX; ++p) c->start[p] = UINT32_MAX;   // never a tile's parameter
+    c->deep = pl.nparams > kPivots;
+    for (int k = 0; k < kPivots; ++k) c->pivot[k] = c->start[c->deep ? k * kPerPivot : k];
+}
+
 // ---- the W-way copies: u = 2-byte units per element
 
 // Parameter p has n tiles per chunk, its first being *nt.
 fsdp_status add_copy_tiles(const Plan& pl, int p, int64_t n, CopyTiles* c, int64_t* nt) {
     if (n * pl.world > INT32_MAX || (*nt + n) * pl.world > INT32_MAX)
         return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
-    c->start[p] = uint32_t(*nt);
+    c->table.start[p] = uint32_t(*nt);
     *nt += n;
     return FSDP_OK;
 }
 
 // The rest of the table, once every parameter has its tiles (nt in a chunk).
 void finish_copy_tiles(const Plan& pl, int64_t nt, CopyTiles* c) {
-    for (int p = pl.nparams; p < PMAX; ++p) c->start[p] = UINT32_MAX;   // never a tile's parameter
-    c->deep = pl.nparams > kPivots;
-    for (int k = 0; k < kPivots; ++k) c->pivot[k] = c->start[c->deep ? k * kPerPivot : k];
+    finish_table(pl, &c->table);
     c->ntiles = uint32_t(nt * pl.world);
     c->per_chunk = uint32_t(nt);
     c->by_chunk = divider(uint32_t(std::max<int64_t>(nt, 1)));
 }
 
-// Whether some segment of the parameter is off the 16-byte grid.
-bool off_grid(const CopyParam& q) { return ((q.off * 2) & 15) || ((q.seg * 2) & 15) || !aligned16(q.data); }
+// Whether every chunk of a bucket buffer starts on a 128-byte line.
+bool chunks_on_lines(const ContigChunks& c, int) { return ((uintptr_t(c.base) | uintptr_t(c.stride)) & 127) == 0; }
+bool chunks_on_lines(const TableChunks& c, int world) {
+    uintptr_t all = 0;
+    for (int i = 0; i < world; ++i) all |= uintptr_t(c.ptr[i]);
+    return (all & 127) == 0;
+}
+// Whether some segment is read off the 16-byte grid or written off the lines:
+// (read, written) are the alignments in bytes of a segment's start and length.
+bool off_grid(int64_t read, int64_t written) { return (read & 15) != 0 || (written & 127) != 0; }
 
 // ---- ag_unpack
 
@@ -1523,10 +1462,9 @@ fsdp_status do_ag_unpack(const Plan& pl, const Chunks& src, const Spans& ins, in
         if ((st = check_param_ptr(params[p], e, 2 * u, p, "params")) != FSDP_OK) return st;
         a.param[p] = {static_cast<uint16_t*>(params[p]), pl.off[p] * u, pl.seg[p] * u, e * u};
         if ((st = add_copy_tiles(pl, p, tiles(pl.seg[p] * u, kCopyTile), &a.tiles, &nt)) != FSDP_OK) return st;
-        // Every tile of segment i of parameter p reads chunk i at off_p and
-        // writes params[p] at i * L_p: all on the 16-byte grid unless a
-        // stride, offset, length or pointer is not.
-        if (off_grid(a.param[p])) any = true;
+        // Segment i of parameter p is read from chunk i at off_p and written
+        // to params[p] at i * L_p.
+        if (off_grid(a.param[p].off * 2, (a.param[p].seg * 2) | int64_t(uintptr_t(params[p])))) any = true;
         if (e > 0) outs.add(params[p], e * 2 * u);
     }
     a.src = src;
@@ -1550,15 +1488,16 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
     RsPackArgs<Chunks> a{};
     Spans ins;
     int64_t nt = 0;               // tiles of one chunk
-    bool any = !chunks_aligned(dst);
+    bool any = !chunks_on_lines(dst, pl.world);
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t e = pl.elems[p];
         if ((st = check_param_ptr(grads[p], e, gsize, p, "grads")) != FSDP_OK) return st;
         a.param[p] = {static_cast<uint16_t*>(const_cast<void*>(grads[p])), pl.off[p] * u, pl.seg[p] * u, e * u};
         const int64_t n = tiles((pl.off[p + 1] - pl.off[p]) * u, kTile);
         if ((st = add_copy_tiles(pl, p, n, &a.tiles, &nt)) != FSDP_OK) return st;
-        // Tiles read grads[p] at j * L_p and write chunk j at off_p.
-        if (off_grid(a.param[p])) any = true;
+        // Segment j of parameter p is read from grads[p] at j * L_p and written
+        // to chunk j at off_p.
+        if (off_grid((a.param[p].seg * 2) | int64_t(uintptr_t(grads[p])), a.param[p].off * 2)) any = true;
         if (e > 0) ins.add(grads[p], e * gsize);
     }
     a.param[pl.nparams].off = pl.chunk * u;
@@ -1572,31 +1511,34 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
 
 // ---- rs_reduce: received elements of type T
 
+template <class Chunks, typename T, int kNB, int kMaxWaves, bool kAny>
+fsdp_status launch_reduce(const Plan& pl, const ReduceArgs<Chunks>& a, hipStream_t stream) {
+    return launch(pl, rs_reduce_kernel<Chunks, T, kNB, kMaxWaves, kAny>, a, int(a.ntiles), kReduceBlock, stream);
+}
+
 template <class Chunks, typename T>
 fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const Spans& ins,
                          float* const* grad_shards, hipStream_t stream) {
     fsdp_status st = FSDP_OK;
     if (grad_shards == nullptr) return fail(FSDP_ERR_INVALID, "grad_shards is NULL");
+    constexpr int64_t tile = int64_t(kReduceBlock) * Unit<T>::kPer;
     Spans outs;
-    int64_t full_tiles = 0;
+    int64_t nt = 0;
+    bool any = !chunks_aligned(src);
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t v = pl.local_elems(p, rank);
         if ((st = check_param_ptr(grad_shards[p], v, 4, p, "grad_shards")) != FSDP_OK) return st;
         if (v > 0) outs.add(grad_shards[p], v * 4);
-        full_tiles += tiles(v, kReduceTile);
+        nt += tiles(v, tile);
+        // Sources of parameter p start at off_p in every chunk.
+        if (((pl.off[p] * int64_t(sizeof(T))) & 15) || !aligned16(grad_shards[p])) any = true;
     }
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
-    if (full_tiles == 0) return FSDP_OK;                 // nothing to write: no launch
-    // A rank's shard that makes fewer than kSmallShardTilesPerCU full-size
-    // tiles per CU is cut into half-size tiles (half as many threads per
-    // workgroup, the same work per thread), so that the workgroups spread
-    // evenly over the CUs.  (The first HIP call: every argument is checked.)
+    if (nt == 0) return FSDP_OK;                         // nothing to write: no launch
+    if (nt > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
+    // (The first HIP call: every argument is checked.)
     const int cus = cu_count(&st);
     if (st != FSDP_OK) return st;
-    bool small = full_tiles < int64_t(kSmallShardTilesPerCU) * cus;
-    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) small = false;
-    if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) small = true;
-    const int64_t tile = small ? kReduceTile / 2 : kReduceTile;
     // Tiles of the parameters with the fewest tiles are numbered (and so
     // dispatched) first: a ragged last tile sums its W sources in a longer
     // dependent chain, which then overlaps the bulk instead of trailing it.
@@ -1611,31 +1553,40 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
         order[q] = p;
     }
     ReduceArgs<Chunks> a{};
-    int64_t nt = 0;
+    int64_t t0 = 0;
     for (int q = 0; q < pl.nparams; ++q) {
         const int p = order[q];
-        a.dst[q] = grad_shards[p];
-        a.off[q] = pl.off[p];
-        a.valid[q] = pl.local_elems(p, rank);
-        a.tile_start[q] = int32_t(nt);
-        nt += nts[p];
-        if (nt > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
+        a.param[q] = {grad_shards[p], pl.off[p], pl.local_elems(p, rank)};
+        a.table.start[q] = uint32_t(t0);
+        t0 += nts[p];
     }
-    for (int q = pl.nparams; q < PMAX; ++q) a.tile_start[q] = INT32_MAX;   // never a tile's parameter
+    finish_table(pl, &a.table);
     a.src = src;
     a.world = pl.world;
-    a.nparams = pl.nparams;
-    a.ntiles = int32_t(nt);
-    // Sources of parameter p start at off_p in every chunk.
-    bool any = false;
-    for (int p = 0; p < pl.nparams; ++p)
-        if (!chunks_aligned(src) || ((pl.off[p] * int64_t(sizeof(T))) & 15)) any = true;
-    if (small) {
-        if (any) return launch(pl, rs_reduce_kernel<Chunks, T, kReduceBlock / 2, true>, a, a.ntiles, kReduceBlock / 2, stream);
-        return launch(pl, rs_reduce_kernel<Chunks, T, kReduceBlock / 2, false>, a, a.ntiles, kReduceBlock / 2, stream);
+    a.ntiles = uint32_t(nt);
+    // The shard's waves per CU decide how many sources a wave keeps in flight
+    // (24-32 KB per CU, as far as the shard goes) and, where they are more than
+    // the CU holds, how many run at once.  Measured, kNB = 1 / 2 / 4: 8B block
+    // at W = 128 (13 waves per CU) 66.8 / 68.0 / 71.3 us; 0.95 M outputs at
+    // W = 64 (7 waves) 24.7 / 21.6 / 22.7; 64 norm shards at W = 32 (1 wave on
+    // every fourth CU) 7.9 / 5.8 / 4.8.  Resident waves per SIMD 3 / 4 / 5: 70B
+    // block, W = 64: 271 / 275 / 281; uneven bucket, W = 48: 384 / 390 / 401;
+    // 8B block, W = 8: 89.9 / 89.0 / 88.5.  Tiles off the grid are added batch
+    // by batch and want two sources: dense uneven bucket 437 us, 488 without a
+    // cap.
+    bool large = nt >= int64_t(kReduceCapWaves) * cus;
+    int batch = nt >= int64_t(kReduceOneWaves) * cus ? 1 : nt >= int64_t(kReduceTwoWaves) * cus ? 2 : 4;
+    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true;
+    if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) large = false, batch = 4;
+    if (any) {
+        if (batch == 4) return launch_reduce<Chunks, T, 4, 8, true>(pl, a, stream);
+        return launch_reduce<Chunks, T, 2, kReduceWaves, true>(pl, a, stream);
     }
-    if (any) return launch(pl, rs_reduce_kernel<Chunks, T, kReduceBlock, true>, a, a.ntiles, kReduceBlock, stream);
-    return launch(pl, rs_reduce_kernel<Chunks, T, kReduceBlock, false>, a, a.ntiles, kReduceBlock, stream);
+    if (large && pl.world >= kReduceWideW) return launch_reduce<Chunks, T, 1, kReduceWaves - 1, false>(pl, a, stream);
+    if (large) return launch_reduce<Chunks, T, 1, kReduceWaves, false>(pl, a, stream);
+    if (batch == 1) return launch_reduce<Chunks, T, 1, 8, false>(pl, a, stream);
+    if (batch == 2) return launch_reduce<Chunks, T, 2, 8, false>(pl, a, stream);
+    return launch_reduce<Chunks, T, 4, 8, false>(pl, a, stream);
 }
 
 }  // namespace

@@ -117,15 +117,15 @@ extern "C" fsdp_status fsdp_bucket_plan_ex(int32_t world_size, int32_t num_param
         pl.reduce_tiles = options->reduce_tiles;
     }
 
-    // Work tiles of each kernel must be countable in 31 bits.
-    int64_t t_pack = 0, t_copy = 0, t_reduce = 0;
+    // Work tiles of the pack and the copies must be countable in 31 bits (the
+    // reduction counts its own when it is called).
+    int64_t t_pack = 0, t_copy = 0;
     for (int p = 0; p < num_params; ++p) {
         const int64_t region = pl.off[p + 1] - pl.off[p];
         t_pack += (region + kPackTile - 1) / kPackTile;
         t_copy += W * ((region + kCopyTile - 1) / kCopyTile);
-        t_reduce += (pl.seg[p] + kReduceTile - 1) / kReduceTile;
     }
-    if (t_pack > INT32_MAX || t_copy > INT32_MAX || t_reduce > INT32_MAX)
+    if (t_pack > INT32_MAX || t_copy > INT32_MAX)
         return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
 
     fsdp_plan* h = new (std::nothrow) fsdp_plan;

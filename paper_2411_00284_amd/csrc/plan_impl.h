@@ -13,10 +13,9 @@ namespace fsdp {
 // that move 8 elements (16 bytes of bf16) per thread and step, kCopySteps
 // steps per tile; ag_pack runs kPackBlock threads that cast 8 elements per
 // thread and step, kPackSteps steps per tile (kPackBigBlock and kPackBigSteps
-// for a large single-chunk pack); the reduction runs kReduceBlock
-// threads that each own kReduceSteps groups of 8 outputs.  One tile per
-// workgroup (small tiles, many workgroups) measured fastest for these HBM
-// streams.
+// for a large single-chunk pack); a reduction tile is one wave with one
+// 16-byte unit of every source per lane.  One tile per workgroup (small tiles,
+// many workgroups) measured fastest for these HBM streams.
 #ifndef FSDP_COPY_BLOCK
 #define FSDP_COPY_BLOCK 128
 #endif
@@ -41,12 +40,6 @@ namespace fsdp {
 #ifndef FSDP_PACK_BIG_STEPS
 #define FSDP_PACK_BIG_STEPS 4
 #endif
-#ifndef FSDP_REDUCE_BLOCK
-#define FSDP_REDUCE_BLOCK 256
-#endif
-#ifndef FSDP_REDUCE_STEPS
-#define FSDP_REDUCE_STEPS 2
-#endif
 constexpr int kVec = 8;
 constexpr int kCopyBlock = FSDP_COPY_BLOCK;
 constexpr int kCopySteps = FSDP_COPY_STEPS;
@@ -63,9 +56,7 @@ constexpr int64_t kPackTile = int64_t(kPackBlock) * kVec * kPackSteps;
 constexpr int kPackBigBlock = FSDP_PACK_BIG_BLOCK;
 constexpr int kPackBigSteps = FSDP_PACK_BIG_STEPS;
 constexpr int64_t kPackBigTile = int64_t(kPackBigBlock) * kVec * kPackBigSteps;
-constexpr int kReduceBlock = FSDP_REDUCE_BLOCK;
-constexpr int kReduceSteps = FSDP_REDUCE_STEPS;
-constexpr int64_t kReduceTile = int64_t(kReduceBlock) * kVec * kReduceSteps;
+constexpr int kReduceBlock = 64;                 // one wave
 
 struct Plan {
     int32_t world;     // W

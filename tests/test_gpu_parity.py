@@ -127,9 +127,9 @@ def wide_bf16_host(words, n):
 
 @pytest.mark.parametrize("tiles", ["full", "half"])
 def test_reduce_tile_sizes(tiles):
-    """The reduction with its tile size forced each way (full-size tiles of 256
-    threads, half-size tiles of 128) on the small buckets, which otherwise
-    take the half-size tiles: every output bit for bit."""
+    """The reduction with its form forced each way (the one for large shards,
+    the one for small ones) on the small buckets, which otherwise take the
+    latter: every output bit for bit."""
     for case in range(len(SMALL)):
         w, dims = SMALL[case]
         plan = BucketPlan(w, dims, reduce_tiles=tiles)
@@ -138,6 +138,37 @@ def test_reduce_tile_sizes(tiles):
         for r in _ranks(w):
             run_rs_reduce(plan, oplan, r, recv)
         plan.close()
+
+
+@pytest.mark.parametrize("align", [8, 1])
+@pytest.mark.parametrize("w,waves_per_cu", [(1, 4), (2, 5), (3, 9), (5, 10), (6, 31), (7, 32), (31, 33), (32, 32), (33, 33)])
+def test_reduce_forms(w, waves_per_cu, align):
+    """Shards on both sides of every size and W at which the reduction changes
+    its form (sources in flight, resident waves), with W on both sides of a
+    batch; ragged ends, and at align = 1 segments off the 16-byte grid."""
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    n = waves_per_cu * cus * 512                              # 64 lanes x 8 outputs
+    dims = [(w * 5, 3), (w * n + 1 - w, 1), (w * 77, 1)]       # the last rank of dim 1 holds fewer
+    plan = BucketPlan(w, dims, align)
+    oplan = O.make_plan(w, dims, align)
+    recv = wide_bf16_host([w, waves_per_cu], w * oplan.chunk)
+    for r in sorted({0, w - 1}):
+        run_rs_reduce(plan, oplan, r, recv)
+    plan.close()
+
+
+@pytest.mark.parametrize("align", [8, 1])
+@pytest.mark.parametrize("shift", [0, 1, 9, 33])
+def test_copy_lines(align, shift):
+    """The copies' stores follow the destination's 128-byte lines: segments
+    shorter than a line, of one line and one element more, of several tiles,
+    with parameter pointers at, before and after a line."""
+    w, dims = 3, [(3 * 63, 1), (3 * 64, 1), (3 * 65, 1), (3 * 7, 1), (5, 129), (3 * 2047, 1), (3 * 2049, 1), (3 * 6001, 1)]
+    plan = BucketPlan(w, dims, align)
+    oplan = O.make_plan(w, dims, align)
+    run_ag_unpack(plan, oplan, seed=7, shift=shift)
+    run_rs_pack(plan, oplan, seed=7, shift=shift)
+    plan.close()
 
 
 @pytest.mark.parametrize("cap", [1, 3, 50])

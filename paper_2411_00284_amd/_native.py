@@ -70,7 +70,12 @@ DTYPE_BF16 = 0
 DTYPE_F32 = 1
 DTYPE_F16 = 2
 
+# The hot calls in the order of _marshal's `op` argument.
+HOT_CALLS = ("fsdp_ag_pack", "fsdp_ag_unpack", "fsdp_rs_pack", "fsdp_rs_reduce", "fsdp_ag_pack_ex",
+             "fsdp_ag_pack_push", "fsdp_ag_unpack_ex", "fsdp_rs_pack_ex", "fsdp_rs_reduce_ex")
+
 _lib = None
+_addresses = None
 
 
 def _hip_runtimes_mapped() -> set[str]:
@@ -105,3 +110,18 @@ def load() -> ctypes.CDLL:
                           "import torch before loading libfsdp_bucket.so")
     _lib = lib
     return lib
+
+
+def caller(plan_handle: int, world_size: int, chunk_elems: int, rows, inner, rows_per_rank):
+    """The native marshaller of one plan's hot calls (csrc/marshal.cpp)."""
+    global _addresses
+    lib = load()
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise ImportError(f"the argument marshaller does not load ({e}): run "
+                          "`python -m paper_2411_00284_amd.build` first; there is no fallback path") from e
+    if _addresses is None:
+        _addresses = tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in HOT_CALLS)
+    return _marshal.Caller(plan_handle, world_size, chunk_elems, tuple(rows), tuple(inner), tuple(rows_per_rank),
+                           _addresses)

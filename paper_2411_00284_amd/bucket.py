@@ -4,6 +4,11 @@ Every step of the path runs in the HIP kernels of ``libfsdp_bucket.so``;
 this module only turns torch tensors into device pointers, checks that their
 dtype, device and element count match the plan, and raises on a non-zero
 status.  torch provides device memory and the current HIP stream.
+
+A hot call first goes through the native marshaller (``csrc/marshal.cpp``),
+which makes the same checks and the library call in one step; a call that it
+does not take (an argument that is wrong, or of a kind it does not know) does
+nothing there and goes through the checks here.
 """
 
 from __future__ import annotations
@@ -19,6 +24,9 @@ from . import _native
 BF16_DTYPES = (torch.bfloat16, torch.int16, torch.uint16)
 F16_DTYPES = (torch.float16,)
 F32_DTYPES = (torch.float32, torch.int32)
+# The hot calls as the native marshaller numbers them.
+(_AG_PACK, _AG_UNPACK, _RS_PACK, _RS_REDUCE, _AG_PACK_EX, _AG_PACK_PUSH, _AG_UNPACK_EX, _RS_PACK_EX,
+ _RS_REDUCE_EX) = range(len(_native.HOT_CALLS))
 _DTYPE_CODES = {"bf16": 0, "f32": 1, "f16": 2}
 _DTYPES = {"bf16": BF16_DTYPES, "f16": F16_DTYPES, "f32": F32_DTYPES}
 
@@ -151,11 +159,14 @@ class BucketPlan:
         self.dims = dims
         self.chunk_elems = int(self._lib.fsdp_plan_chunk_elems(h))
         self._param = []
+        c, o, L = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
+        out = ctypes.byref(c), ctypes.byref(o), ctypes.byref(L)
         for p in range(n):
-            c, o, L = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
-            _check(self._lib.fsdp_plan_param(h, p, ctypes.byref(c), ctypes.byref(o), ctypes.byref(L)),
-                   "fsdp_plan_param")
+            _check(self._lib.fsdp_plan_param(h, p, *out), "fsdp_plan_param")
             self._param.append((c.value, o.value, L.value))
+        self._caller = _native.caller(h.value, self.world_size, self.chunk_elems, [d[0] for d in dims],
+                                      [d[1] for d in dims], [q[0] for q in self._param])
+        self._run = self._caller.run
 
     # ---- plan queries
     def rows_per_rank(self, p: int) -> int:
@@ -182,6 +193,9 @@ class BucketPlan:
     # ---- the hot path
     def ag_pack(self, rank: int, shards: Sequence[torch.Tensor], send_chunk: torch.Tensor, stream=None) -> None:
         """fp32 Shard(0) slabs of ``rank`` -> bf16 send chunk of S elements."""
+        done = self._run(_AG_PACK, rank, shards, send_chunk, 0, stream)
+        if done is not None:
+            return _check(done, "fsdp_ag_pack")
         self._check_len(shards, "shards")
         arr = _ptr_array(shards, [self.local_elems(p, rank) for p in range(self.num_params)],
                          (torch.float32,), "shards")
@@ -191,6 +205,9 @@ class BucketPlan:
 
     def ag_unpack(self, gathered: torch.Tensor, params: Sequence[torch.Tensor], stream=None) -> None:
         """Rank-major W*S bf16 buffer -> full bf16 parameters."""
+        done = self._run(_AG_UNPACK, 0, params, gathered, 0, stream)
+        if done is not None:
+            return _check(done, "fsdp_ag_unpack")
         self._check_len(params, "params")
         src = _bucket_ptr(gathered, self.world_size * self.chunk_elems, BF16_DTYPES, "gathered")
         arr = _ptr_array(params, [self.full_elems(p) for p in range(self.num_params)], BF16_DTYPES, "params")
@@ -199,6 +216,9 @@ class BucketPlan:
 
     def rs_pack(self, grads: Sequence[torch.Tensor], send_buf: torch.Tensor, stream=None) -> None:
         """Full bf16 gradients -> destination-major W*S bf16 send buffer."""
+        done = self._run(_RS_PACK, 0, grads, send_buf, 0, stream)
+        if done is not None:
+            return _check(done, "fsdp_rs_pack")
         self._check_len(grads, "grads")
         arr = _ptr_array(grads, [self.full_elems(p) for p in range(self.num_params)], BF16_DTYPES, "grads")
         dst = _bucket_ptr(send_buf, self.world_size * self.chunk_elems, BF16_DTYPES, "send_buf")
@@ -207,6 +227,9 @@ class BucketPlan:
 
     def rs_reduce(self, rank: int, recv: torch.Tensor, grad_shards: Sequence[torch.Tensor], stream=None) -> None:
         """Source-major W*S bf16 buffer -> fp32 gradient shards of ``rank`` (average over ranks)."""
+        done = self._run(_RS_REDUCE, rank, grad_shards, recv, 0, stream)
+        if done is not None:
+            return _check(done, "fsdp_rs_reduce")
         self._check_len(grad_shards, "grad_shards")
         src = _bucket_ptr(recv, self.world_size * self.chunk_elems, BF16_DTYPES, "recv")
         arr = _ptr_array(grad_shards, [self.local_elems(p, rank) for p in range(self.num_params)],
@@ -218,6 +241,9 @@ class BucketPlan:
     def ag_pack_ex(self, rank: int, shards: Sequence[torch.Tensor], send_chunk: torch.Tensor,
                    param_dtype: str = "bf16", stream=None) -> None:
         """fp32 shards -> a chunk of ``param_dtype`` ("bf16" or "f16" cast, or "f32" copy)."""
+        done = self._run(_AG_PACK_EX, rank, shards, send_chunk, _DTYPE_CODES.get(param_dtype, -1), stream)
+        if done is not None:
+            return _check(done, "fsdp_ag_pack_ex")
         self._check_len(shards, "shards")
         arr = _ptr_array(shards, [self.local_elems(p, rank) for p in range(self.num_params)],
                          (torch.float32,), "shards")
@@ -229,6 +255,9 @@ class BucketPlan:
                      param_dtype: str = "bf16", stream=None) -> None:
         """fp32 shards -> the packed chunk of ``param_dtype``, written to each of the W
         ``chunks`` (where every rank receives this rank's chunk)."""
+        done = self._run(_AG_PACK_PUSH, rank, shards, chunks, _DTYPE_CODES.get(param_dtype, -1), stream)
+        if done is not None:
+            return _check(done, "fsdp_ag_pack_push")
         self._check_len(shards, "shards")
         arr = _ptr_array(shards, [self.local_elems(p, rank) for p in range(self.num_params)],
                          (torch.float32,), "shards")
@@ -239,6 +268,9 @@ class BucketPlan:
     def ag_unpack_ex(self, chunks: Sequence[torch.Tensor], params: Sequence[torch.Tensor],
                      param_dtype: str = "bf16", stream=None) -> None:
         """W gathered chunks (rank i's at chunks[i]) -> full parameters of ``param_dtype``."""
+        done = self._run(_AG_UNPACK_EX, 0, params, chunks, _DTYPE_CODES.get(param_dtype, -1), stream)
+        if done is not None:
+            return _check(done, "fsdp_ag_unpack_ex")
         self._check_len(params, "params")
         carr = self._chunk_array(chunks, _elem_dtypes(param_dtype))
         arr = _ptr_array(params, [self.full_elems(p) for p in range(self.num_params)],
@@ -250,6 +282,9 @@ class BucketPlan:
                    reduce_dtype: str = "bf16", stream=None) -> None:
         """Full gradients (bf16, f16 or fp32) -> W destination chunks of ``reduce_dtype``
         (the gradients' type, or "f32")."""
+        done = self._run(_RS_PACK_EX, 0, grads, chunks, _DTYPE_CODES.get(reduce_dtype, -1), stream)
+        if done is not None:
+            return _check(done, "fsdp_rs_pack_ex")
         self._check_len(grads, "grads")
         names = {_dtype_name(g) for g in grads if g is not None}
         if len(names) > 1:
@@ -263,6 +298,9 @@ class BucketPlan:
     def rs_reduce_ex(self, rank: int, chunks: Sequence[torch.Tensor], grad_shards: Sequence[torch.Tensor],
                      reduce_dtype: str = "bf16", stream=None) -> None:
         """W received chunks (source i's at chunks[i]) of ``reduce_dtype`` -> fp32 shards of ``rank``."""
+        done = self._run(_RS_REDUCE_EX, rank, grad_shards, chunks, _DTYPE_CODES.get(reduce_dtype, -1), stream)
+        if done is not None:
+            return _check(done, "fsdp_rs_reduce_ex")
         self._check_len(grad_shards, "grad_shards")
         carr = self._chunk_array(chunks, _elem_dtypes(reduce_dtype))
         arr = _ptr_array(grad_shards, [self.local_elems(p, rank) for p in range(self.num_params)],
@@ -285,6 +323,8 @@ class BucketPlan:
 
     def close(self) -> None:
         if getattr(self, "_h", None) is not None and self._h.value:
+            if getattr(self, "_caller", None) is not None:
+                self._caller.close()
             self._lib.fsdp_plan_free(self._h)
             self._h = ctypes.c_void_p()
 

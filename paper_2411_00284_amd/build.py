@@ -18,6 +18,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -29,6 +30,7 @@ LIB_PATH = os.path.join(PKG, LIB_NAME)
 # Reference streams for the benchmark's ceiling leg: a library of their own,
 # not loaded by the package.
 PROBES_PATH = os.path.join(PKG, "libfsdp_probes.so")
+MARSHAL_PATH = os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")
@@ -75,12 +77,29 @@ def build(verbose: bool = False, defines=(), out_dir: str | None = None) -> str:
     os.replace(tmp, lib_path)
     if variant:
         return lib_path
+    _build_marshal(verbose)
     pobj = os.path.join(BUILD, "ceiling_probes.o")
     _run([HIPCC, *DEVICE_FLAGS, *inc, "-c", os.path.join(CSRC, "ceiling_probes.hip"), "-o", pobj], verbose)
     tmp = PROBES_PATH + f".tmp{os.getpid()}"
     _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, pobj], verbose)
     os.replace(tmp, PROBES_PATH)
     return LIB_PATH
+
+
+def _build_marshal(verbose: bool) -> None:
+    """The binding's argument marshalling: a CPython extension against torch's
+    headers (host code; the bucket library stays free of torch and Python)."""
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    inc = [f"-I{INCLUDE}", f"-I{os.path.join(ROCM, 'include')}", f"-I{sysconfig.get_paths()['include']}",
+           f"-isystem{os.path.join(troot, 'include')}",
+           f"-isystem{os.path.join(troot, 'include', 'torch', 'csrc', 'api', 'include')}"]
+    tmp = MARSHAL_PATH + f".tmp{os.getpid()}"
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+          f"-D_GLIBCXX_USE_CXX11_ABI={abi}", *inc, os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
+          f"-L{os.path.join(troot, 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
+    os.replace(tmp, MARSHAL_PATH)
 
 
 def clean() -> None:

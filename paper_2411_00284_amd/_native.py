@@ -76,6 +76,7 @@ HOT_CALLS = ("fsdp_ag_pack", "fsdp_ag_unpack", "fsdp_rs_pack", "fsdp_rs_reduce",
 
 _lib = None
 _addresses = None
+_caller_type = None
 
 
 def _hip_runtimes_mapped() -> set[str]:
@@ -114,14 +115,15 @@ def load() -> ctypes.CDLL:
 
 def caller(plan_handle: int, world_size: int, chunk_elems: int, rows, inner, rows_per_rank):
     """The native marshaller of one plan's hot calls (csrc/marshal.cpp)."""
-    global _addresses
-    lib = load()
-    try:
-        from . import _marshal
-    except ImportError as e:
-        raise ImportError(f"the argument marshaller does not load ({e}): run "
-                          "`python -m paper_2411_00284_amd.build` first; there is no fallback path") from e
+    global _addresses, _caller_type
     if _addresses is None:
+        lib = load()
+        try:
+            from ._marshal import Caller
+        except ImportError as e:
+            raise ImportError(f"the argument marshaller does not load ({e}): run "
+                              "`python -m paper_2411_00284_amd.build` first; there is no fallback path") from e
+        _caller_type = Caller
         _addresses = tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in HOT_CALLS)
-    return _marshal.Caller(plan_handle, world_size, chunk_elems, tuple(rows), tuple(inner), tuple(rows_per_rank),
+    return _caller_type(plan_handle, world_size, chunk_elems, tuple(rows), tuple(inner), tuple(rows_per_rank),
                            _addresses)

@@ -179,6 +179,9 @@ class BucketPlan:
         return self._param[p][2]
 
     def local_rows(self, p: int, rank: int) -> int:
+        if 0 <= p < self.num_params and 0 <= rank < self.world_size and self._h:
+            n, c = self.dims[p][0], self._param[p][0]
+            return min(c, max(0, n - rank * c))
         r = int(self._lib.fsdp_plan_local_rows(self._h, p, rank))
         if r < 0:
             raise ValueError(f"bad parameter {p} or rank {rank}")

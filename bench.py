@@ -50,17 +50,17 @@ KERNELS = ("ag_pack", "ag_unpack", "rs_pack", "rs_reduce")
 # wave keeps in flight and the resident waves per SIMD, by the waves (of 512
 # outputs) that the rank's shard makes; a single-chunk pack of fewer than 4 big
 # (256-thread, 4-step) tiles per CU packs with 128-thread, 1-step tiles.
-# The copies and the reduce have a second form ("true") that the library
-# launches when some segment of the bucket is read off the 16-byte grid or
-# (the copies) written off the 128-byte lines.
+# Every kernel has a second form ("true") that the library launches when some
+# segment of the bucket is off the 16-byte grid (the copies: or written off the
+# 128-byte lines).
 KERNEL_SYMBOLS = {
-    "ag_pack": "ag_pack_kernel<1, OneChunk, 256, 4>",
+    "ag_pack": "ag_pack_kernel<1, OneChunk, 256, 4, false>",
     "ag_unpack": "ag_unpack_kernel<ContigChunks, false>",
     "rs_pack": "rs_pack_kernel<ContigChunks, 0, false>",
     "rs_reduce": "rs_reduce_kernel<ContigChunks, unsigned short, 1, 3, false>",
 }
 REDUCE_SMALL_SYMBOL = "rs_reduce_kernel<ContigChunks, unsigned short, 4, 8, false>"
-PACK_SMALL_SYMBOL = "ag_pack_kernel<1, OneChunk, 128, 1>"
+PACK_SMALL_SYMBOL = "ag_pack_kernel<1, OneChunk, 128, 1, false>"
 KERNEL_BASENAMES = ("ag_pack_kernel", "ag_unpack_kernel", "rs_pack_kernel", "rs_reduce_kernel", "probe_read_kernel",
                     "probe_fill_kernel", "probe_copy_kernel", "probe_cast_kernel", "probe_reduce_kernel",
                     "probe_empty_kernel")
@@ -117,8 +117,9 @@ def kernel_symbol(name, plan, rank, cus):
         form = reduce_form(waves / cus, plan.world_size, any(o % 16 for o in [2 * S] + offsets))
         return "rs_reduce_kernel<ContigChunks, unsigned short, %d, %d, %s>" % form
     if name == "ag_pack":
-        if pack_tiles(plan, PACK_BIG_TILE) < PACK_BIG_TILES_PER_CU * cus:
-            return PACK_SMALL_SYMBOL
+        small = pack_tiles(plan, PACK_BIG_TILE) < PACK_BIG_TILES_PER_CU * cus
+        sym = PACK_SMALL_SYMBOL if small else KERNEL_SYMBOLS[name]
+        return sym.replace("false>", "true>") if any(o % 16 for o in offsets) else sym
     return KERNEL_SYMBOLS[name]
 
 

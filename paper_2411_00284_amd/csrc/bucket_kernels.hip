@@ -558,12 +558,74 @@ struct PackLane {
     }
 };
 
+// A tile whose shard or whose place in the chunk is off the 16-byte grid (a
+// dense bucket, A < 8, or a shard that is a view of flat storage): units of 4
+// elements, loaded from any fp32 address and stored along the destination's
+// 128-byte lines (several destinations share only the 16-byte grid), as in
+// seg_copy_any.  The elements before the first line and units cut by the
+// shard's or the region's end go one by one.  Two steps at a time: more keep
+// no more in flight than HBM takes, and cost registers.
+template <int kOut, class Dst, bool kNt, int kB, int kS>
+__device__ __forceinline__ void pack_tile_any(const PackArgs<Dst>& a, const PackParam& pp, int64_t lo, int64_t hi) {
+    constexpr bool kOne = std::is_same<Dst, OneChunk>::value;
+    typedef typename std::conditional<kOut != kF32, uint16_t, uint32_t>::type Out;
+    constexpr int kU = 4, kUnits = kB * kVec * kS / kU;
+    constexpr int kLine = (kOne ? 128 : 16) / int(sizeof(Out));   // elements
+    constexpr int kBytes = kU * int(sizeof(Out));
+    constexpr int kPolicy = kNt ? kPolicyNt : 0;
+    const int64_t v = pp.valid, region = pp.region;
+    const int ndst = kOne ? 1 : a.ndst;
+    const int t = threadIdx.x;
+    const Out* const d0 = reinterpret_cast<const Out*>(a.dst.at(0)) + pp.off;
+    const int h = (kLine - (int(reinterpret_cast<uintptr_t>(d0 + lo) / sizeof(Out)) & (kLine - 1))) & (kLine - 1);
+    const int64_t at = lo + h;                                    // the first line at or after lo
+    const auto cast = [](float f) { return Out(kOut != kF32 ? cast1<kOut>(f) : __float_as_uint(f)); };
+    if (lo == 0 && t < h)
+        for (int j = 0; j < ndst; ++j)
+            copy_elements<1>(pp.src, reinterpret_cast<Out*>(a.dst.at(j)) + pp.off, t, v, min(at, hi), cast);
+    const int nu = clamp_to((hi - at + kLine - 1) / kLine * kLine / kU, kUnits);
+    const int whole = clamp_to((min(v, region) - at) >> 2, nu);
+    const int zero_from = clamp_to((v - at + kU - 1) >> 2, nu), zero_to = clamp_to((region - at) >> 2, nu);
+    const char* const from = as_global(reinterpret_cast<const char*>(pp.src + at));
+#pragma unroll 1
+    for (int u0 = 0; u0 < nu; u0 += 2 * kB) {
+        u32x4 x[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = u0 + u * kB + t;
+            x[u] = u32x4{0, 0, 0, 0};
+            if (i < whole)
+                x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any4*>(from + uint32_t(i) * (kU * 4)));
+        }
+        for (int j = 0; j < ndst; ++j) {
+            Out* const d = reinterpret_cast<Out*>(a.dst.at(j)) + pp.off;
+            const Window out = window(d + at, uint32_t(nu) * kBytes);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int i = u0 + u * kB + t;
+                const bool unit = i < whole || (i >= zero_from && i < zero_to);
+                const uint32_t byte = unit ? uint32_t(i) * kBytes : ~0u;    // past the window: dropped
+                if constexpr (kOut == kF32) {
+                    __builtin_amdgcn_raw_buffer_store_b128(x[u], out, int(byte), 0, kPolicy);
+                } else {
+                    const float4 f = {__uint_as_float(x[u].x), __uint_as_float(x[u].y), __uint_as_float(x[u].z),
+                                      __uint_as_float(x[u].w)};
+                    const uint2 c = cast4<kOut>(f);
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{c.x, c.y}, out, int(byte), 0, kPolicy);
+                }
+                if (!unit && i < nu) copy_elements<kU>(pp.src, d, at + int64_t(i) * kU, v, region, cast);
+            }
+        }
+    }
+}
+
 // Tile lt of parameter pp: its part of [off_p, off_{p+1}) of the chunk, the
 // shard's values cast to bf16 or fp16 or copied as fp32 (kOut), zeros past the shard,
 // written to every destination.  Each thread handles 4 elements per sub-step
 // (16 bytes of fp32 in), so every load and store instruction of a wave covers
 // one contiguous run; the full tiles of a 16-bit push take 8 per thread.
-template <int kOut, class Dst, bool kNt = true, int kB = kPackBlock, int kS = kPackSteps>
+// kAny: some parameter is off the 16-byte grid (the host picks it only then).
+template <int kOut, class Dst, bool kAny, bool kNt = true, int kB = kPackBlock, int kS = kPackSteps>
 __device__ __forceinline__ void pack_tile(const PackArgs<Dst>& a, const PackParam& pp, int lt) {
     constexpr int64_t kTile = int64_t(kB) * kVec * kS;
     constexpr bool kCast = kOut != kF32;
@@ -580,6 +642,12 @@ __device__ __forceinline__ void pack_tile(const PackArgs<Dst>& a, const PackPara
     if (lo >= hi) return;
     // every destination chunk is 16-byte aligned, so one test covers them all
     const bool vec = is_aligned16(src) && is_aligned16(reinterpret_cast<Out*>(a.dst.at(0)) + off);
+    if constexpr (kAny) {
+        if (!vec) {
+            pack_tile_any<kOut, Dst, kNt, kB, kS>(a, pp, lo, hi);
+            return;
+        }
+    }
     if constexpr (!kOne && kCast) {
         // Pushed to W destinations, the stores outnumber the loads W to 1:
         // each thread casts 8 consecutive elements and writes them with one
@@ -648,14 +716,14 @@ __device__ __forceinline__ void pack_tile(const PackArgs<Dst>& a, const PackPara
 // wait before the data loads is the one round of table loads.  The big tile's
 // registers are held to 64 so that 8 waves fit on each SIMD (the extra lane
 // fields had cost one wave).  A tile is kB threads x kS steps of 8 elements.
-template <int kOut, class Dst, int kB, int kS>
+template <int kOut, class Dst, int kB, int kS, bool kAny>
 __global__ void __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(8))) ag_pack_kernel(const PackArgs<Dst> a) {
     const PackLane lane(a);
     int64_t step = blockIdx.x;
     do {
         const int t = int(step);
         const int p = param_of_tile(lane.start, t);
-        pack_tile<kOut, Dst, true, kB, kS>(a, lane.param(p), t - __builtin_amdgcn_readlane(lane.start, p));
+        pack_tile<kOut, Dst, kAny, true, kB, kS>(a, lane.param(p), t - __builtin_amdgcn_readlane(lane.start, p));
         step += gridDim.x;
     } while (step < a.ntiles);
 }
@@ -664,14 +732,14 @@ __global__ void __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(8))) ag
 // cache so that the copies to the other destinations read it back from L2 and
 // the MALL.  (Read back at once by many workgroups, a chunk just written with
 // non-temporal stores streamed at little more than half the rate.)
-template <int kOut>
+template <int kOut, bool kAny>
 __global__ void __launch_bounds__(kPackBlock) push_pack_kernel(const PackArgs<OneChunk> a) {
     const PackLane lane(a);
     int64_t step = blockIdx.x;
     do {
         const int t = int(step);
         const int p = param_of_tile(lane.start, t);
-        pack_tile<kOut, OneChunk, false>(a, lane.param(p), t - __builtin_amdgcn_readlane(lane.start, p));
+        pack_tile<kOut, OneChunk, kAny, false>(a, lane.param(p), t - __builtin_amdgcn_readlane(lane.start, p));
         step += gridDim.x;
     } while (step < a.ntiles);
 }
@@ -1328,6 +1396,20 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 // ---- ag_pack
 
+template <int kOut, class Dst>
+fsdp_status launch_pack(const Plan& pl, const PackArgs<Dst>& a, bool big, bool cached, bool any, hipStream_t stream) {
+    if constexpr (std::is_same<Dst, OneChunk>::value) {
+        if (cached && any) return launch(pl, push_pack_kernel<kOut, true>, a, a.ntiles, kPackBlock, stream);
+        if (cached) return launch(pl, push_pack_kernel<kOut, false>, a, a.ntiles, kPackBlock, stream);
+        if (big && any)
+            return launch(pl, ag_pack_kernel<kOut, Dst, kPackBigBlock, kPackBigSteps, true>, a, a.ntiles, kPackBigBlock, stream);
+        if (big)
+            return launch(pl, ag_pack_kernel<kOut, Dst, kPackBigBlock, kPackBigSteps, false>, a, a.ntiles, kPackBigBlock, stream);
+    }
+    if (any) return launch(pl, ag_pack_kernel<kOut, Dst, kPackBlock, kPackSteps, true>, a, a.ntiles, kPackBlock, stream);
+    return launch(pl, ag_pack_kernel<kOut, Dst, kPackBlock, kPackSteps, false>, a, a.ntiles, kPackBlock, stream);
+}
+
 // `dst` is the send chunk (OneChunk) or the W destination chunks
 // (TableChunks); `outs` holds their byte spans for the overlap check.
 template <class Dst>
@@ -1339,6 +1421,7 @@ fsdp_status do_ag_pack(const Plan& pl, int32_t rank, const float* const* shards,
     PackArgs<Dst> a{};
     Spans ins;
     int64_t nt = 0, nt_big = 0;   // at most the planner's checked pack tile count
+    bool any = false;
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t v = pl.local_elems(p, rank);
         if ((st = check_param_ptr(shards[p], v, 4, p, "shards")) != FSDP_OK) return st;
@@ -1347,6 +1430,8 @@ fsdp_status do_ag_pack(const Plan& pl, int32_t rank, const float* const* shards,
         a.valid[p] = v;
         nt += tiles(pl.off[p + 1] - pl.off[p], kPackTile);
         nt_big += tiles(pl.off[p + 1] - pl.off[p], kPackBigTile);
+        // Every destination chunk is 16-byte aligned (the host has checked).
+        if (!aligned16(shards[p]) || ((pl.off[p] * elem_bytes(wire)) & 15)) any = true;
         if (v > 0) ins.add(shards[p], v * 4);
     }
     a.off[pl.nparams] = pl.chunk;
@@ -1375,25 +1460,9 @@ fsdp_status do_ag_pack(const Plan& pl, int32_t rank, const float* const* shards,
     }
     for (int p = pl.nparams; p < PMAX; ++p) a.tile_start[p] = INT32_MAX;   // never a tile's parameter
     a.ntiles = int32_t(t0);
-    if (big) {
-        if (wire == FSDP_DTYPE_BF16)
-            return launch(pl, ag_pack_kernel<kBF16, Dst, kPackBigBlock, kPackBigSteps>, a, a.ntiles, kPackBigBlock, stream);
-        if (wire == FSDP_DTYPE_F16)
-            return launch(pl, ag_pack_kernel<kF16, Dst, kPackBigBlock, kPackBigSteps>, a, a.ntiles, kPackBigBlock, stream);
-        return launch(pl, ag_pack_kernel<kF32, Dst, kPackBigBlock, kPackBigSteps>, a, a.ntiles, kPackBigBlock, stream);
-    }
-    if constexpr (std::is_same<Dst, OneChunk>::value) {
-        if (cached) {
-            if (wire == FSDP_DTYPE_BF16) return launch(pl, push_pack_kernel<kBF16>, a, a.ntiles, kPackBlock, stream);
-            if (wire == FSDP_DTYPE_F16) return launch(pl, push_pack_kernel<kF16>, a, a.ntiles, kPackBlock, stream);
-            return launch(pl, push_pack_kernel<kF32>, a, a.ntiles, kPackBlock, stream);
-        }
-    }
-    if (wire == FSDP_DTYPE_BF16)
-        return launch(pl, ag_pack_kernel<kBF16, Dst, kPackBlock, kPackSteps>, a, a.ntiles, kPackBlock, stream);
-    if (wire == FSDP_DTYPE_F16)
-        return launch(pl, ag_pack_kernel<kF16, Dst, kPackBlock, kPackSteps>, a, a.ntiles, kPackBlock, stream);
-    return launch(pl, ag_pack_kernel<kF32, Dst, kPackBlock, kPackSteps>, a, a.ntiles, kPackBlock, stream);
+    if (wire == FSDP_DTYPE_BF16) return launch_pack<kBF16>(pl, a, big, cached, any, stream);
+    if (wire == FSDP_DTYPE_F16) return launch_pack<kF16>(pl, a, big, cached, any, stream);
+    return launch_pack<kF32>(pl, a, big, cached, any, stream);
 }
 
 fsdp_status do_ag_pack_one(const fsdp_plan* h, int32_t rank, const float* const* shards, fsdp_dtype wire,

@@ -168,6 +168,20 @@ def test_copy_lines(align, shift):
     oplan = O.make_plan(w, dims, align)
     run_ag_unpack(plan, oplan, seed=7, shift=shift)
     run_rs_pack(plan, oplan, seed=7, shift=shift)
+    for r in range(w):
+        run_ag_pack(plan, oplan, r, seed=7, shift=shift)
+    plan.close()
+
+
+@pytest.mark.parametrize("align,shift", [(8, 1), (1, 0), (1, 3)])
+def test_pack_big_tiles_off_the_grid(align, shift):
+    """The single-chunk pack's big tiles with shards and segments off the
+    16-byte grid, ragged at every parameter's end."""
+    w, dims = 2, [(3, 7), (2000, 4096 * 2 + 3), (5, 3), (7777, 517)]
+    plan = BucketPlan(w, dims, align)
+    oplan = O.make_plan(w, dims, align)
+    for r in range(w):
+        run_ag_pack(plan, oplan, r, seed=911, shift=shift)
     plan.close()
 
 

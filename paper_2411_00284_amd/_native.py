@@ -113,7 +113,7 @@ def load() -> ctypes.CDLL:
     return lib
 
 
-def caller(plan_handle: int, world_size: int, chunk_elems: int, rows, inner, rows_per_rank):
+def caller(plan_handle: int, world_size: int, chunk_elems: int, dims: list):
     """The native marshaller of one plan's hot calls (csrc/marshal.cpp)."""
     global _addresses, _caller_type
     if _addresses is None:
@@ -124,6 +124,5 @@ def caller(plan_handle: int, world_size: int, chunk_elems: int, rows, inner, row
             raise ImportError(f"the argument marshaller does not load ({e}): run "
                               "`python -m paper_2411_00284_amd.build` first; there is no fallback path") from e
         _caller_type = Caller
-        _addresses = tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in HOT_CALLS)
-    return _caller_type(plan_handle, world_size, chunk_elems, tuple(rows), tuple(inner), tuple(rows_per_rank),
-                           _addresses)
+        _addresses = tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in (*HOT_CALLS, "fsdp_plan_param"))
+    return _caller_type(plan_handle, world_size, chunk_elems, dims, _addresses)

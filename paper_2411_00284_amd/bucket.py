@@ -158,14 +158,8 @@ class BucketPlan:
         self.align = int(align)
         self.dims = dims
         self.chunk_elems = int(self._lib.fsdp_plan_chunk_elems(h))
-        self._param = []
-        c, o, L = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
-        out = ctypes.byref(c), ctypes.byref(o), ctypes.byref(L)
-        for p in range(n):
-            _check(self._lib.fsdp_plan_param(h, p, *out), "fsdp_plan_param")
-            self._param.append((c.value, o.value, L.value))
-        self._caller = _native.caller(h.value, self.world_size, self.chunk_elems, [d[0] for d in dims],
-                                      [d[1] for d in dims], [q[0] for q in self._param])
+        self._caller = _native.caller(h.value, self.world_size, self.chunk_elems, dims)
+        self._param = self._caller.params()
         self._run = self._caller.run
 
     # ---- plan queries

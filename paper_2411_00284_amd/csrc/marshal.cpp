@@ -32,11 +32,13 @@ namespace {
 // passes and of the `op` argument of a call.
 enum Op { kAgPack, kAgUnpack, kRsPack, kRsReduce, kAgPackEx, kAgPackPush, kAgUnpackEx, kRsPackEx, kRsReduceEx, kOps };
 
+struct Param {
+    int64_t rows, inner, cpr, off, seg;      // N_p, inner_p, c_p, off_p, L_p
+};
+
 struct Caller {
     PyObject_HEAD
-    std::vector<int64_t>* rows;      // N_p
-    std::vector<int64_t>* inner;     // inner_p
-    std::vector<int64_t>* cpr;       // c_p
+    std::vector<Param>* params;
     int64_t chunk;                   // S
     const fsdp_plan* plan;
     int32_t world;
@@ -120,7 +122,7 @@ PyObject* run_checked(Caller* self, PyObject* const* args) {
     const bool shards = op == kAgPack || op == kAgPackEx || op == kAgPackPush || op == kRsReduce || op == kRsReduceEx;
     const bool packed = op == kAgPack || op == kAgPackEx;           // one chunk
     const Items items(args[2]);
-    const int P = int(self->rows->size());
+    const int P = int(self->params->size());
     if (items.n != P || P > FSDP_MAX_PARAMS) Py_RETURN_NONE;
     fsdp_dtype own = op == kRsPackEx ? FSDP_DTYPE_BF16 : fsdp_dtype(wire);
     if (op == kRsPackEx && !gradient_code(items, &own)) Py_RETURN_NONE;
@@ -128,9 +130,9 @@ PyObject* run_checked(Caller* self, PyObject* const* args) {
     Checked c;
     void* tensors[FSDP_MAX_PARAMS];
     for (int p = 0; p < P; ++p) {
-        const int64_t n = (*self->rows)[p], rows = (*self->cpr)[p];
-        const int64_t held = shards ? std::min(rows, std::max<int64_t>(0, n - rank * rows)) : n;
-        const int64_t elems = held * (*self->inner)[p];
+        const Param& q = (*self->params)[p];
+        const int64_t held = shards ? std::min(q.cpr, std::max<int64_t>(0, q.rows - rank * q.cpr)) : q.rows;
+        const int64_t elems = held * q.inner;
         if (items.at[p] == Py_None) {
             if (elems != 0) Py_RETURN_NONE;
             tensors[p] = nullptr;
@@ -233,18 +235,18 @@ PyObject* caller_run(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     }
 }
 
-// Caller(plan, world, chunk, rows, inner, rows_per_rank, addresses)
+// Caller(plan, world, chunk, dims, addresses): `dims` is the list of (rows,
+// inner) of the parameters, `addresses` the hot calls' and fsdp_plan_param's.
 PyObject* caller_new(PyTypeObject* type, PyObject* args, PyObject*) {
     unsigned long long plan;
     int world;
     long long chunk;
-    PyObject *rows, *inner, *cpr, *fns;
-    if (!PyArg_ParseTuple(args, "KiLO!O!O!O!", &plan, &world, &chunk, &PyTuple_Type, &rows, &PyTuple_Type, &inner,
-                          &PyTuple_Type, &cpr, &PyTuple_Type, &fns))
+    PyObject *dims, *fns;
+    if (!PyArg_ParseTuple(args, "KiLO!O!", &plan, &world, &chunk, &PyList_Type, &dims, &PyTuple_Type, &fns))
         return nullptr;
-    const Py_ssize_t P = PyTuple_GET_SIZE(rows);
-    if (PyTuple_GET_SIZE(inner) != P || PyTuple_GET_SIZE(cpr) != P || PyTuple_GET_SIZE(fns) != kOps) {
-        PyErr_SetString(PyExc_ValueError, "tables of different lengths");
+    const Py_ssize_t P = PyList_GET_SIZE(dims);
+    if (PyTuple_GET_SIZE(fns) != kOps + 1) {
+        PyErr_SetString(PyExc_ValueError, "addresses of another library");
         return nullptr;
     }
     auto* self = reinterpret_cast<Caller*>(type->tp_alloc(type, 0));
@@ -252,32 +254,56 @@ PyObject* caller_new(PyTypeObject* type, PyObject* args, PyObject*) {
     self->plan = reinterpret_cast<const fsdp_plan*>(uintptr_t(plan));
     self->world = world;
     self->chunk = chunk;
+    for (int k = 0; k < kOps; ++k) self->fn[k] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(fns, k));
+    const auto query = reinterpret_cast<decltype(&fsdp_plan_param)>(PyLong_AsVoidPtr(PyTuple_GET_ITEM(fns, kOps)));
+    if (PyErr_Occurred()) {
+        Py_DECREF(self);
+        return nullptr;
+    }
     try {
-        self->rows = new std::vector<int64_t>;
-        self->inner = new std::vector<int64_t>;
-        self->cpr = new std::vector<int64_t>;
+        self->params = new std::vector<Param>;
+        self->params->reserve(size_t(P));
         for (Py_ssize_t p = 0; p < P; ++p) {
-            self->rows->push_back(PyLong_AsLongLong(PyTuple_GET_ITEM(rows, p)));
-            self->inner->push_back(PyLong_AsLongLong(PyTuple_GET_ITEM(inner, p)));
-            self->cpr->push_back(PyLong_AsLongLong(PyTuple_GET_ITEM(cpr, p)));
+            long long rows, inner;
+            if (!PyArg_ParseTuple(PyList_GET_ITEM(dims, p), "LL", &rows, &inner)) {
+                Py_DECREF(self);
+                return nullptr;
+            }
+            Param q{rows, inner, 0, 0, 0};
+            if (query(self->plan, int32_t(p), &q.cpr, &q.off, &q.seg) != FSDP_OK) {
+                Py_DECREF(self);
+                PyErr_SetString(PyExc_ValueError, "unknown plan");
+                return nullptr;
+            }
+            self->params->push_back(q);
         }
     } catch (...) {
         Py_DECREF(self);
         return PyErr_NoMemory();
     }
-    for (int k = 0; k < kOps; ++k) self->fn[k] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(fns, k));
-    if (PyErr_Occurred()) {
-        Py_DECREF(self);
-        return nullptr;
-    }
     return reinterpret_cast<PyObject*>(self);
+}
+
+// params() -> [(c_p, off_p, L_p)]
+PyObject* caller_params(PyObject* o, PyObject*) {
+    const auto& params = *reinterpret_cast<Caller*>(o)->params;
+    PyObject* list = PyList_New(Py_ssize_t(params.size()));
+    if (!list) return nullptr;
+    for (size_t p = 0; p < params.size(); ++p) {
+        PyObject* t = Py_BuildValue("(LLL)", static_cast<long long>(params[p].cpr), static_cast<long long>(params[p].off),
+                                    static_cast<long long>(params[p].seg));
+        if (!t) {
+            Py_DECREF(list);
+            return nullptr;
+        }
+        PyList_SET_ITEM(list, Py_ssize_t(p), t);
+    }
+    return list;
 }
 
 void caller_dealloc(PyObject* o) {
     auto* self = reinterpret_cast<Caller*>(o);
-    delete self->rows;
-    delete self->inner;
-    delete self->cpr;
+    delete self->params;
     Py_TYPE(o)->tp_free(o);
 }
 
@@ -290,6 +316,7 @@ PyObject* caller_close(PyObject* self, PyObject*) {
 PyMethodDef caller_methods[] = {
     {"run", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(caller_run)), METH_FASTCALL,
      "run(op, rank, tensors, bucket, dtype, stream) -> status, or None when nothing was done"},
+    {"params", caller_params, METH_NOARGS, "(rows per rank, offset, segment elements) of every parameter"},
     {"close", caller_close, METH_NOARGS, "forget the plan"},
     {nullptr, nullptr, 0, nullptr}};
 

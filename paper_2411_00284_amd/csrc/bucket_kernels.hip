@@ -6,12 +6,12 @@
 // rank's segment of a parameter), so that a tile is a plain contiguous copy,
 // cast or reduction with 16-byte vector accesses.  The per-parameter table
 // travels in the kernel arguments.  The pack and the reduce number their tiles
-// parameter by parameter and hold the table in lanes (lane p holds parameter
-// p's entries; a ballot over the first tiles finds a tile's parameter).  The
-// W-way copies number theirs chunk by chunk and look a tile up with scalar
-// instructions only (CopyTiles).  Tile counts fit in 31 bits (the planner
-// checks); grid-stride loops count in 64 bits, or in unsigned 32 (a tile
-// number plus a grid size is below 2^32), so the last step cannot overflow.
+// parameter by parameter, the W-way copies chunk by chunk.  The pack holds the
+// table in lanes (lane p holds parameter p's entries; a ballot over the first
+// tiles finds a tile's parameter); the others look a tile up with scalar
+// instructions only (TilePlace).  Tile counts fit in 31 bits (checked on the
+// host); grid-stride loops count in 64 bits, or in unsigned 32 (a tile number
+// plus a grid size is below 2^32), so the last step cannot overflow.
 //
 // A bucket buffer of W chunks is addressed either as one allocation (chunk i
 // at base + i*stride) or through a table of W chunk pointers, so the same
@@ -68,9 +68,9 @@ namespace {
 
 constexpr int PMAX = FSDP_MAX_PARAMS;
 constexpr int kMaxChunks = FSDP_MAX_CHUNKS;
-// One parameter per lane of a wave64: the ballot lookup and the lane-held
-// tables need every parameter's entry in one wavefront.
-static_assert(PMAX <= 64, "the tile lookup holds one parameter per lane of a 64-wide wavefront");
+// One parameter per lane of a wave64: the pack's ballot lookup and lane-held
+// table need every parameter's entry in one wavefront.
+static_assert(PMAX <= 64, "the pack's lookup holds one parameter per lane of a 64-wide wavefront");
 static_assert(kCopyBlock % 64 == 0 && kWidenBlock % 64 == 0 && kPackBlock % 64 == 0 && kPackBigBlock % 64 == 0 &&
                   kReduceBlock == 64,
               "workgroups are whole wavefronts, the reduction's one wavefront");
@@ -127,22 +127,6 @@ __device__ __forceinline__ float widen_lo(uint32_t w) { return kFrom == kF16 ? f
 template <int kFrom>
 __device__ __forceinline__ float widen_hi(uint32_t w) { return kFrom == kF16 ? f16_hi(w) : bf16_hi(w); }
 
-#ifndef FSDP_LDS_TABLE
-#define FSDP_LDS_TABLE 0
-#endif
-
-#if FSDP_LDS_TABLE
-// A measured alternative to reading the tile table from the kernel arguments:
-// the first wave stages entries 0..63 (INT_MAX from n on) in LDS, and after a
-// barrier every lane reads its entry there.
-__device__ __forceinline__ int staged_entry(const int32_t* table, int n) {
-    __shared__ int staged[64];
-    if (threadIdx.x < 64) staged[threadIdx.x] = int(threadIdx.x) < n ? table[threadIdx.x] : INT_MAX;
-    __syncthreads();
-    return staged[threadIdx.x & 63];
-}
-#endif
-
 // Parameter owning tile t: the last p with tile_start[p] <= t.  Every lane of
 // the wave holds tile_start[lane] (INT_MAX past the last parameter).
 __device__ __forceinline__ int param_of_tile(int my_start, int t) {
@@ -173,16 +157,7 @@ typedef f32x4 __attribute__((aligned(4))) f32x4_any4;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef u32x2 __attribute__((aligned(2))) u32x2_any2;
 
-// 16-byte accesses; streamed data bypasses cache retention (non-temporal).
-__device__ __forceinline__ uint4 ld16(const void* p) {
-    const u32x4* q = reinterpret_cast<const u32x4*>(p);
-#if FSDP_NT_LOAD
-    const u32x4 v = __builtin_nontemporal_load(q);
-#else
-    const u32x4 v = *q;
-#endif
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
+// The pack's accesses; streamed data bypasses cache retention (non-temporal).
 // Stores are non-temporal unless kNt is false: a chunk that other workgroups
 // read back at once (the first half of a wide push) is stored through the cache.
 template <bool kNt = bool(FSDP_NT_STORE)>
@@ -193,15 +168,6 @@ __device__ __forceinline__ void st16(void* p, uint4 v) {
     else *q = w;
 }
 
-__device__ __forceinline__ uint2 ld8(const void* p) {
-    const u32x2* q = reinterpret_cast<const u32x2*>(p);
-#if FSDP_NT_LOAD
-    const u32x2 v = __builtin_nontemporal_load(q);
-#else
-    const u32x2 v = *q;
-#endif
-    return make_uint2(v.x, v.y);
-}
 template <bool kNt = bool(FSDP_NT_STORE)>
 __device__ __forceinline__ void st8(void* p, uint2 v) {
     u32x2* q = reinterpret_cast<u32x2*>(p);
@@ -515,7 +481,12 @@ struct PackParam {
 // tile table, then the entries of the parameter it names).  from_lane is only
 // called where every lane of the wave is active, on values every lane wrote:
 // a lane that is inactive when a value is computed keeps its old register,
-// and readlane would return that.  The pack and the reduce use them.
+// and readlane would return that.  The pack uses them: its look-up runs at the
+// start of the launch, where no streams are in the way of a vector load, and
+// one round of those is shorter than TilePlace's two or three scalar rounds
+// (a 10 MB pack 5.1 us this way, 5.9 with TilePlace; the copies and the
+// reduction, whose workgroups keep starting among running streams, are the
+// other way round).
 __device__ __forceinline__ int lane_index() { return int(threadIdx.x & 63); }
 // The table entry a lane loads: its own, or the last one for the lanes past
 // PMAX (none while PMAX is the wavefront width; their tile start is INT_MAX,
@@ -542,11 +513,7 @@ struct PackLane {
     template <class Dst>
     __device__ __forceinline__ explicit PackLane(const PackArgs<Dst>& a) {
         const int l = table_lane();
-#if FSDP_LDS_TABLE
-        start = staged_entry(a.tile_start, PMAX);
-#else
         start = lane_index() < PMAX ? a.tile_start[l] : INT_MAX;
-#endif
         src = a.src[l];
         off = a.off[l];
         end = a.off[l + 1];
@@ -822,11 +789,11 @@ __global__ void __launch_bounds__(kCopyBlock) replicate_grouped_kernel(const Rep
 // dies (XCDs) round-robin, so in tile order b each die would take every 8th
 // 4 KB tile.  Instead, within each group of 8 * kXcdRun tiles, the workgroups
 // of one die (b, b + 8, b + 16, ...) take kXcdRun consecutive tiles, a 1 MB
-// run per die (1.4 % faster rs_pack and 1 % faster unpack on the 70B block,
-// 1-3 % on the other Llama blocks and the uneven bucket; runs of 16 tiles
-// were 8 % slower, and the reduce gained nothing from such an order); the
-// tiles past the last whole group keep order b.  A bijection
-// on [0, n), so a grid-stride loop over b still covers every tile once.
+// run per die.  Against it, on the 8B, 70B and 405B blocks and the uneven
+// bucket: plain order 1-3 % slower, runs of 16 tiles 8 %, of 128, 512 and 1024
+// 0-3 %; the reduce gained nothing from such an order.  The tiles past the last
+// whole group keep order b.  A bijection on [0, n), so a grid-stride loop over
+// b still covers every tile once.
 __device__ __forceinline__ uint32_t copy_tile(uint32_t b, uint32_t n) {
     constexpr uint32_t kGroup = uint32_t(kXcds) * kXcdRun;
     if (b >= n / kGroup * kGroup) return b;

@@ -173,7 +173,10 @@ class BucketPlan:
         return self._param[p][2]
 
     def local_rows(self, p: int, rank: int) -> int:
-        if 0 <= p < self.num_params and 0 <= rank < self.world_size and self._h:
+        # Plain ints only: arithmetic on a numpy integer keeps its width and
+        # overflows, and a float is no rank; the library takes or refuses those.
+        plain = type(p) is int and type(rank) is int
+        if plain and 0 <= p < self.num_params and 0 <= rank < self.world_size and self._h:
             n, c = self.dims[p][0], self._param[p][0]
             return min(c, max(0, n - rank * c))
         r = int(self._lib.fsdp_plan_local_rows(self._h, p, rank))

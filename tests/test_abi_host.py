@@ -187,6 +187,27 @@ def test_plan_queries_on_bad_input():
     assert LIB.fsdp_plan_chunk_elems(None) == -1
 
 
+@pytest.mark.parametrize("rank", [np.int8(100), np.uint8(5), np.int32(5), np.int64(127), torch.tensor(3), True])
+def test_local_rows_of_any_integer(rank):
+    """A rank of any integer type, its width too small for the rows included."""
+    plan = BucketPlan(128, [(128 * 256, 3), (128256, 1)])
+    for p, rows in enumerate((256, 1002)):
+        got = plan.local_rows(p, rank)
+        assert type(got) is int and got == rows
+        assert plan.local_rows(np.int8(p), rank) == rows
+        assert plan.local_elems(p, rank) == rows * plan.dims[p][1]
+    plan.close()
+
+
+@pytest.mark.parametrize("bad", [1.0, np.float64(1), "1", None])
+def test_local_rows_of_no_integer(bad):
+    plan = BucketPlan(4, [(8, 3), (9, 1)])
+    for args in ((0, bad), (bad, 0)):
+        with pytest.raises(ctypes.ArgumentError):
+            plan.local_rows(*args)
+    plan.close()
+
+
 def test_status_strings():
     for code in range(8):
         assert LIB.fsdp_status_str(code)

@@ -1612,7 +1612,7 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     // cap.
     bool large = nt >= int64_t(kReduceCapWaves) * cus;
     int batch = nt >= int64_t(kReduceOneWaves) * cus ? 1 : nt >= int64_t(kReduceTwoWaves) * cus ? 2 : 4;
-    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true;
+    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true, batch = 1;
     if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) large = false, batch = 4;
     if (any) {
         if (batch == 4) return launch_reduce<Chunks, T, 4, 8, true>(pl, a, stream);

@@ -140,6 +140,20 @@ def test_reduce_tile_sizes(tiles):
         plan.close()
 
 
+@pytest.mark.parametrize("tiles", ["full", "half"])
+@pytest.mark.parametrize("align,shift", [(1, 0), (8, 1), (1, 3)])
+def test_reduce_tile_sizes_off_the_grid(tiles, align, shift):
+    """The same with segments or outputs off the 16-byte grid."""
+    for case in range(len(SMALL)):
+        w, dims = SMALL[case]
+        plan = BucketPlan(w, dims, align, reduce_tiles=tiles)
+        oplan = O.make_plan(w, dims, align)
+        recv = wide_bf16_host([case, 78], w * oplan.chunk)
+        for r in _ranks(w):
+            run_rs_reduce(plan, oplan, r, recv, shift=shift)
+        plan.close()
+
+
 @pytest.mark.parametrize("align", [8, 1])
 @pytest.mark.parametrize("w,waves_per_cu", [(1, 4), (2, 5), (3, 9), (5, 10), (6, 31), (7, 32), (31, 33), (32, 32), (33, 33)])
 def test_reduce_forms(w, waves_per_cu, align):

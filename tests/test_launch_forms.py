@@ -1,0 +1,67 @@
+"""Which kernel each call launches, on the host: the library is loaded against
+a stub of the HIP runtime that records launches by kernel name and runs
+nothing (a child process, so that the real runtime is not in the way)."""
+
+from __future__ import annotations
+
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_2411_00284_amd", "libfsdp_bucket.so")
+CUS = 256
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """calls -> the kernels that each launched; and the names of all kernels."""
+    stub = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["gcc", "-std=gnu99", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                    os.path.join(HERE, "hip_stub.c"), "-o", stub], check=True)
+
+    def demangled(names):
+        out = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True, check=True).stdout
+        return [n.replace("fsdp::(anonymous namespace)::", "").split("(", 1)[0].removeprefix("void ") for n in out.splitlines()]
+
+    def run(calls):
+        res = subprocess.run([sys.executable, os.path.join(HERE, "launch_worker.py"), stub, LIB], text=True,
+                             input=json.dumps(calls), capture_output=True, timeout=120)
+        assert res.returncode == 0, res.stderr
+        got = json.loads(res.stdout)
+        assert got["cus"] == CUS
+        return [demangled(names) for names in got["launched"]], demangled(got["kernels"])
+
+    return run
+
+
+def shard_of(world, tiles, per_tile=512):
+    """A bucket whose rank 0 holds `tiles` reduction tiles (one parameter)."""
+    return [[world * tiles * per_tile, 1]]
+
+
+# What puts a reduction off the 16-byte grid: a segment's offset, the chunks'
+# stride (one buffer only), an output.
+OFF_GRID = {"offset": {"dims": [[9, 1], [64, 64]], "align": 1}, "stride": {"dims": [[28, 1]], "align": 1},
+            "output": {"dims": [[64, 64]], "shift": 4}}
+
+
+@pytest.mark.parametrize("why", OFF_GRID)
+@pytest.mark.parametrize("tiles,form", [("full", "2, 4, true"), ("half", "4, 8, true"), ("auto", "4, 8, true")])
+def test_forced_reduce_form_off_the_grid(launches, why, tiles, form):
+    """A small shard off the grid: reduce_tiles="full" forces the form for
+    large shards there too."""
+    got, _ = launches([{"call": "rs_reduce", "world": 4, "tiles": tiles, **OFF_GRID[why]}])
+    assert got == [[f"rs_reduce_kernel<ContigChunks, unsigned short, {form}>"]]
+
+
+@pytest.mark.parametrize("tiles,form", [("full", "1, 4, false"), ("half", "4, 8, false"), ("auto", "4, 8, false")])
+def test_forced_reduce_form(launches, tiles, form):
+    got, _ = launches([{"call": "rs_reduce", "world": 4, "tiles": tiles, "dims": [[64, 64]]},
+                       {"call": "rs_reduce", "world": 4, "tiles": tiles, "dims": shard_of(4, 64 * CUS)}])
+    assert got[0] == [f"rs_reduce_kernel<ContigChunks, unsigned short, {form}>"]
+    if tiles != "auto":
+        assert got[1] == got[0]

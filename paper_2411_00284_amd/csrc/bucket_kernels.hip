@@ -1086,7 +1086,8 @@ __device__ __forceinline__ float sum_one(const Chunks& src, int W, int64_t at) {
 // instruction writes one contiguous run (stored as two halves per lane, every
 // 128-byte line is written in two parts: 330 us instead of 285 on the 70B
 // block's shape).  No other wave reads it, so no barrier is needed: a wave's
-// LDS accesses stay in order.
+// LDS accesses stay in order, and the fences keep the compiler's order of them
+// (release for the lanes' writes, acquire for the reads of other lanes').
 template <int kB, int kRows, bool kDirect, int kPer>
 __device__ __forceinline__ void store_units(float* tile, uint32_t units, const float (&acc)[kRows][kPer], float wf) {
     __shared__ f32x4 stage[kPer == 8 ? kB * 2 : 1];
@@ -1101,11 +1102,11 @@ __device__ __forceinline__ void store_units(float* tile, uint32_t units, const f
             f32x4* const mine = stage + wave * 2;
             mine[lane * 2] = f32x4{acc[r][0] / wf, acc[r][1] / wf, acc[r][2] / wf, acc[r][3] / wf};
             mine[lane * 2 + 1] = f32x4{acc[r][4] / wf, acc[r][5] / wf, acc[r][6] / wf, acc[r][7] / wf};
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             out[0] = mine[lane];
             out[1] = mine[64 + lane];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll

@@ -1541,8 +1541,10 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
     a.dst = dst;
     finish_copy_tiles(pl, nt, &a.tiles);
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
-    // (The widening pack has its own checks and no misaligned vector path.)
-    if (kWiden == kF32 && any) return launch(pl, rs_pack_kernel<Chunks, kWiden, true>, a, int(a.tiles.ntiles), kBlock, stream);
+    // (The widening pack takes any address in its one form: seg_widen chooses tile by tile.)
+    if constexpr (kWiden == kF32) {
+        if (any) return launch(pl, rs_pack_kernel<Chunks, kWiden, true>, a, int(a.tiles.ntiles), kBlock, stream);
+    }
     return launch(pl, rs_pack_kernel<Chunks, kWiden, false>, a, int(a.tiles.ntiles), kBlock, stream);
 }
 

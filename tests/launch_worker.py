@@ -42,7 +42,9 @@ def main():
         n = len(dims)
         plan, options = ctypes.c_void_p(), Options(0, TILES[c.get("tiles", "auto")], 0)
         rows, inner = (ctypes.c_int64 * n)(*[d[0] for d in dims]), (ctypes.c_int64 * n)(*[d[1] for d in dims])
-        assert lib.fsdp_bucket_plan_ex(W, n, rows, inner, c.get("align", 8), ctypes.byref(options), ctypes.byref(plan)) == 0
+        status = lib.fsdp_bucket_plan_ex(W, n, rows, inner, c.get("align", 8), ctypes.byref(options),
+                                         ctypes.byref(plan))
+        assert status == 0, c
         S = lib.fsdp_plan_chunk_elems(plan)
         local = [lib.fsdp_plan_local_rows(plan, p, rank) * dims[p][1] for p in range(n)]
         wire = c.get("wire", "bf16")

@@ -4,8 +4,10 @@ nothing (a child process, so that the real runtime is not in the way)."""
 
 from __future__ import annotations
 
+import itertools
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -18,14 +20,16 @@ CUS = 256
 
 @pytest.fixture(scope="module")
 def launches(tmp_path_factory):
-    """calls -> the kernels that each launched; and the names of all kernels."""
+    """calls -> the kernels that each launched; and the names of all kernels
+    in the library's device code (whose symbols end in .kd)."""
     stub = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
     subprocess.run(["gcc", "-std=gnu99", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
                     os.path.join(HERE, "hip_stub.c"), "-o", stub], check=True)
 
     def demangled(names):
         out = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True, check=True).stdout
-        return [n.replace("fsdp::(anonymous namespace)::", "").split("(", 1)[0].removeprefix("void ") for n in out.splitlines()]
+        return [n.replace("fsdp::(anonymous namespace)::", "").split("(", 1)[0].removeprefix("void ")
+                for n in out.splitlines()]
 
     def run(calls):
         res = subprocess.run([sys.executable, os.path.join(HERE, "launch_worker.py"), stub, LIB], text=True,
@@ -33,7 +37,10 @@ def launches(tmp_path_factory):
         assert res.returncode == 0, res.stderr
         got = json.loads(res.stdout)
         assert got["cus"] == CUS
-        return [demangled(names) for names in got["launched"]], demangled(got["kernels"])
+        with open(LIB, "rb") as f:
+            built = {n.decode() for n in re.findall(rb"(_ZN4fsdp\w+)\.kd", f.read())}
+        assert set(got["kernels"]) <= built
+        return [demangled(names) for names in got["launched"]], demangled(sorted(built))
 
     return run
 
@@ -65,3 +72,33 @@ def test_forced_reduce_form(launches, tiles, form):
     assert got[0] == [f"rs_reduce_kernel<ContigChunks, unsigned short, {form}>"]
     if tiles != "auto":
         assert got[1] == got[0]
+
+
+def every_form():
+    """Calls that between them take every branch of the dispatch."""
+    small, large = [[64, 64], [9, 64]], [[64, 64], [40_000_000, 1]]
+    odd = {"shift": 4, "align": 1}
+    calls = []
+    for wire in ("bf16", "f16", "f32"):
+        for off in ({}, odd):
+            calls += [{"call": "ag_pack_ex", "world": 2, "dims": dims, "wire": wire, **off} for dims in (small, large)]
+            calls += [{"call": "ag_pack_push", "world": w, "dims": small, "wire": wire, **off} for w in (4, 8, 20)]
+            calls += [{"call": "rs_pack_ex", "world": 4, "dims": small, "wire": wire, **off},
+                      {"call": "ag_unpack_ex", "world": 4, "dims": small, "wire": wire, **off}]
+            if wire != "f32":
+                calls += [{"call": "rs_pack_ex", "world": 4, "dims": small, "wire": "f32", "grad": wire, **off}]
+    calls += [{"call": c, "world": 4, "dims": small, **off}
+              for c in ("ag_pack", "ag_unpack", "rs_pack") for off in ({}, odd)]
+    reduces = [("rs_reduce", "bf16"), ("rs_reduce_ex", "bf16"), ("rs_reduce_ex", "f16"), ("rs_reduce_ex", "f32")]
+    for world, waves, (call, wire) in itertools.product((2, 8, 40), (1, 7, 20, 40, 70, 100), reduces):
+        dims = shard_of(world, waves * CUS, 256 if wire == "f32" else 512)
+        calls += [{"call": call, "world": world, "wire": wire, "dims": dims},
+                  {"call": call, "world": world, "wire": wire, "dims": [[9, 1], *dims], "align": 1}]
+    return calls
+
+
+def test_every_kernel_is_reached(launches):
+    """No kernel is built that no call launches."""
+    launched, kernels = launches(every_form())
+    assert all(launched)
+    assert sorted(set(kernels) - {k for names in launched for k in names}) == []

@@ -52,14 +52,14 @@ KERNELS = ("ag_pack", "ag_unpack", "rs_pack", "rs_reduce")
 # (256-thread, 4-step) tiles per CU packs with 128-thread, 1-step tiles.
 # Every kernel has a second form ("true") that the library launches when some
 # segment of the bucket is off the 16-byte grid (the copies: or written off the
-# 128-byte lines).
+# 128-byte lines); the reduce's last flag says that its tiles are dealt in runs.
 KERNEL_SYMBOLS = {
     "ag_pack": "ag_pack_kernel<1, OneChunk, 256, 4, false>",
     "ag_unpack": "ag_unpack_kernel<ContigChunks, false>",
     "rs_pack": "rs_pack_kernel<ContigChunks, 0, false>",
-    "rs_reduce": "rs_reduce_kernel<ContigChunks, unsigned short, 1, 3, false>",
+    "rs_reduce": "rs_reduce_kernel<ContigChunks, unsigned short, 1, 3, false, false>",
 }
-REDUCE_SMALL_SYMBOL = "rs_reduce_kernel<ContigChunks, unsigned short, 4, 8, false>"
+REDUCE_SMALL_SYMBOL = "rs_reduce_kernel<ContigChunks, unsigned short, 4, 8, false, false>"
 PACK_SMALL_SYMBOL = "ag_pack_kernel<1, OneChunk, 128, 1, false>"
 KERNEL_BASENAMES = ("ag_pack_kernel", "ag_unpack_kernel", "rs_pack_kernel", "rs_reduce_kernel", "probe_read_kernel",
                     "probe_fill_kernel", "probe_copy_kernel", "probe_cast_kernel", "probe_reduce_kernel",
@@ -91,14 +91,16 @@ def algorithmic_bytes(W, S, E, V0):
     }
 
 
-def reduce_form(waves_per_cu, world_size, off_grid):
-    """The reduce's template numbers: sources in flight, resident waves, off-grid form."""
+def reduce_form(waves_per_cu, world_size, off_grid, off_lines):
+    """The reduce's template numbers: sources in flight, resident waves,
+    off-grid form, tiles in runs (`off_lines`: most of them are off the lines)."""
     batch = 1 if waves_per_cu >= REDUCE_ONE_WAVES else 2 if waves_per_cu >= REDUCE_TWO_WAVES else 4
+    runs = "true" if off_lines and batch < 4 else "false"
     if off_grid:
-        return (4, 8, "true") if batch == 4 else (2, 4, "true")
+        return (4, 8, "true", "false") if batch == 4 else (2, 4, "true", runs)
     if waves_per_cu >= REDUCE_CAP_WAVES:
-        return (1, 3 if world_size >= REDUCE_WIDE_W else 4, "false")
-    return (batch, 8, "false")
+        return (1, 3 if world_size >= REDUCE_WIDE_W else 4, "false", runs)
+    return (batch, 8, "false", runs)
 
 
 def kernel_symbol(name, plan, rank, cus):
@@ -113,9 +115,11 @@ def kernel_symbol(name, plan, rank, cus):
         off_grid = any(n % 16 for n in segs) or any(o % 128 for o in [2 * S] + offsets)
         return KERNEL_SYMBOLS[name].replace("false>", "true>") if off_grid else KERNEL_SYMBOLS[name]
     if name == "rs_reduce":
-        waves = sum(-(-plan.local_elems(p, rank) // REDUCE_TILE) for p in range(P))
-        form = reduce_form(waves / cus, plan.world_size, any(o % 16 for o in [2 * S] + offsets))
-        return "rs_reduce_kernel<ContigChunks, unsigned short, %d, %d, %s>" % form
+        waves = [-(-plan.local_elems(p, rank) // REDUCE_TILE) for p in range(P)]
+        off = sum(w for w, o in zip(waves, offsets) if o % 128 or 2 * S % 128)
+        form = reduce_form(sum(waves) / cus, plan.world_size, any(o % 16 for o in [2 * S] + offsets),
+                           2 * off > sum(waves))
+        return "rs_reduce_kernel<ContigChunks, unsigned short, %d, %d, %s, %s>" % form
     if name == "ag_pack":
         small = pack_tiles(plan, PACK_BIG_TILE) < PACK_BIG_TILES_PER_CU * cus
         sym = PACK_SMALL_SYMBOL if small else KERNEL_SYMBOLS[name]

@@ -79,6 +79,7 @@ constexpr int kReduceCapWaves = FSDP_REDUCE_CAP_WAVES;    // waves per CU from w
 constexpr int kReduceWideW = 32;                          // ... and W from which one wave fewer is resident
 constexpr int kReduceOneWaves = FSDP_REDUCE_ONE_WAVES;    // ... from which a wave keeps one source in flight, not two
 constexpr int kReduceTwoWaves = FSDP_REDUCE_TWO_WAVES;    // ... two sources, not four
+constexpr int kReduceFewW = 4;                            // sources up to which fp32 outputs always write through
 constexpr int kBlocksPerCU = FSDP_BLOCKS_PER_CU;  // workgroups per CU in the grid-stride launch
 constexpr int kXcds = 8;                          // accelerator dies; workgroup b runs on die b % 8
 constexpr int kXcdRun = FSDP_XCD_RUN;             // consecutive copy tiles dealt to one die
@@ -219,8 +220,9 @@ __device__ __forceinline__ u32x4 ld16(Window w, uint32_t byte) {
 __device__ __forceinline__ u32x2 ld8(Window w, uint32_t byte) {
     return __builtin_amdgcn_raw_buffer_load_b64(w, int(byte), 0, FSDP_LOAD_POLICY);
 }
+template <int kPolicy = FSDP_STORE_POLICY>
 __device__ __forceinline__ void st16(Window w, uint32_t byte, u32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, w, int(byte), 0, FSDP_STORE_POLICY);
+    __builtin_amdgcn_raw_buffer_store_b128(v, w, int(byte), 0, kPolicy);
 }
 __device__ __forceinline__ void st16(Window w, uint32_t byte, f32x4 v) { st16(w, byte, __builtin_bit_cast(u32x4, v)); }
 
@@ -791,8 +793,8 @@ __global__ void __launch_bounds__(kCopyBlock) replicate_grouped_kernel(const Rep
 // of one die (b, b + 8, b + 16, ...) take kXcdRun consecutive tiles, a 1 MB
 // run per die.  Against it, on the 8B, 70B and 405B blocks and the uneven
 // bucket: plain order 1-3 % slower, runs of 16 tiles 8 %, of 128, 512 and 1024
-// 0-3 %; the reduce gained nothing from such an order.  The tiles past the last
-// whole group keep order b.  A bijection on [0, n), so a grid-stride loop over
+// 0-3 %.  (The reduce takes it where its tiles share lines.)  The tiles past the
+// last whole group keep order b.  A bijection on [0, n), so a grid-stride loop over
 // b still covers every tile once.
 __device__ __forceinline__ uint32_t copy_tile(uint32_t b, uint32_t n) {
     constexpr uint32_t kGroup = uint32_t(kXcds) * kXcdRun;
@@ -1088,8 +1090,11 @@ __device__ __forceinline__ float sum_one(const Chunks& src, int W, int64_t at) {
 // block's shape).  No other wave reads it, so no barrier is needed: a wave's
 // LDS accesses stay in order, and the fences keep the compiler's order of them
 // (release for the lanes' writes, acquire for the reads of other lanes').
+//
+// through: the stores write through.
 template <int kB, int kRows, bool kDirect, int kPer>
-__device__ __forceinline__ void store_units(float* tile, uint32_t units, const float (&acc)[kRows][kPer], float wf) {
+__device__ __forceinline__ void store_units(float* tile, uint32_t units, const float (&acc)[kRows][kPer], float wf,
+                                            bool through) {
     __shared__ f32x4 stage[kPer == 8 ? kB * 2 : 1];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x & ~63u;
     const uint32_t quads = units * (kPer / 4);       // 16-byte outputs of the tile
@@ -1113,7 +1118,10 @@ __device__ __forceinline__ void store_units(float* tile, uint32_t units, const f
         for (int h = 0; h < kPer / 4; ++h) {
             const uint32_t q = (r * kB + wave) * (kPer / 4) + h * 64 + lane;
             if constexpr (kDirect) {
-                st16(window(tile, quads * 16), q * 16, out[h]);
+                const Window to = window(tile, quads * 16);
+                const u32x4 y = __builtin_bit_cast(u32x4, out[h]);
+                if (through) st16(to, q * 16, y);
+                else st16<kPolicyNt>(to, q * 16, y);
             } else {
                 if (q < quads) __builtin_nontemporal_store(out[h], reinterpret_cast<f32x4_any4*>(tile + q * 4));
             }
@@ -1121,15 +1129,29 @@ __device__ __forceinline__ void store_units(float* tile, uint32_t units, const f
     }
 }
 
+// Whether a tile's averages are written through.  A tile that starts off the
+// lines shares its first and last line with its neighbours, and written through
+// such a line goes to memory in parts: 46.2 us so, 44.4 through the cache (bf16
+// wire, W = 8, 100 waves per CU, shards 16 bytes off the lines; on them the
+// check costs nothing that shows, but 0.1 us in the smallest shards' form,
+// which is without it).  With an fp32
+// wire of few sources the outputs are a large part of the traffic, and it is
+// better for them not to wait in the L2: W = 2, 17.1 us against 18.5.
+template <typename T>
+__device__ __forceinline__ bool store_through(const float* out, int W) {
+    return on_line(out) || (Unit<T>::kPer == 4 && W <= kReduceFewW);
+}
+
 // A tile of a reduction: elements [first, first + n) of every chunk, n <= kElems.
-template <int kElems>
+// kRuns: the tiles are dealt to the dies in runs (copy_tile).
+template <int kElems, bool kRuns>
 struct ReduceSpot {
     int64_t first;
     uint32_t n;
     float* out;
     template <class Args>
     __device__ __forceinline__ ReduceSpot(const Args& a, uint32_t step) {
-        const TilePlace at(a.table, step);
+        const TilePlace at(a.table, kRuns ? copy_tile(step, a.ntiles) : step);
         ReduceParam q = a.param[at.param];
         asm volatile("" : "+s"(q.dst), "+s"(q.off), "+s"(q.valid));   // one load, here
         const int64_t lo = int64_t(at.tile) * kElems;
@@ -1155,13 +1177,14 @@ struct ReduceSpot {
 //
 // kAny: some parameter's sources or outputs are off the 16-byte grid (the
 // host picks it only then).  Such tiles load and store at any element, and a
-// batch is added before the next one is loaded.
-template <class Chunks, typename T, int kNB, int kMaxWaves, bool kAny>
+// batch is added before the next one is loaded.  kRuns: see the host's choice
+// of it.
+template <class Chunks, typename T, int kNB, int kMaxWaves, bool kAny, bool kRuns>
 __global__ void __launch_bounds__(kReduceBlock)
 __attribute__((amdgpu_waves_per_eu(kMaxWaves < 8 ? kMaxWaves : kNB > 2 ? 4 : 8, kMaxWaves)))
 rs_reduce_kernel(const ReduceArgs<Chunks> a) {
     constexpr int kPer = Unit<T>::kPer;
-    typedef ReduceSpot<kReduceBlock * kPer> Spot;
+    typedef ReduceSpot<kReduceBlock * kPer, kRuns> Spot;
     const uint32_t t = threadIdx.x;
     const int W = a.world;
     const float wf = float(W);
@@ -1175,10 +1198,10 @@ rs_reduce_kernel(const ReduceArgs<Chunks> a) {
             float acc[1][kPer];
             if (a.src.aligned() && (byte & 15) == 0 && is_aligned16(s.out)) {
                 sum_units<T, kReduceBlock, 1, kNB, true>(acc, a.src, W, byte, units);
-                store_units<kReduceBlock, 1, true>(s.out, units, acc, wf);
+                store_units<kReduceBlock, 1, true>(s.out, units, acc, wf, kNB > 2 || store_through<T>(s.out, W));
             } else {
                 sum_units<T, kReduceBlock, 1, kNB, false>(acc, a.src, W, byte, units);
-                store_units<kReduceBlock, 1, false>(s.out, units, acc, wf);
+                store_units<kReduceBlock, 1, false>(s.out, units, acc, wf, false);
             }
             const uint32_t k = units * kPer + t;                  // fewer than kPer elements are left
             if (k < s.n) s.out[k] = sum_one<T, 4>(a.src, W, s.first + k) / wf;
@@ -1225,7 +1248,7 @@ rs_reduce_kernel(const ReduceArgs<Chunks> a) {
         __builtin_amdgcn_sched_barrier(0);
         add(x[1], W - j - kNB);
         const uint32_t units = s.n / kPer;
-        store_units<kReduceBlock, 1, true>(s.out, units, acc, wf);
+        store_units<kReduceBlock, 1, true>(s.out, units, acc, wf, kNB > 2 || store_through<T>(s.out, W));
         const uint32_t k = units * kPer + t;                      // fewer than kPer elements are left
         if (k < s.n) s.out[k] = sum_one<T, 4>(a.src, W, s.first + k) / wf;
     } while (step < a.ntiles);
@@ -1550,9 +1573,15 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
 
 // ---- rs_reduce: received elements of type T
 
-template <class Chunks, typename T, int kNB, int kMaxWaves, bool kAny>
+template <class Chunks, typename T, int kNB, int kMaxWaves, bool kAny, bool kRuns>
 fsdp_status launch_reduce(const Plan& pl, const ReduceArgs<Chunks>& a, hipStream_t stream) {
-    return launch(pl, rs_reduce_kernel<Chunks, T, kNB, kMaxWaves, kAny>, a, int(a.ntiles), kReduceBlock, stream);
+    return launch(pl, rs_reduce_kernel<Chunks, T, kNB, kMaxWaves, kAny, kRuns>, a, int(a.ntiles), kReduceBlock, stream);
+}
+
+template <class Chunks, typename T, int kNB, int kMaxWaves>
+fsdp_status launch_reduce(const Plan& pl, const ReduceArgs<Chunks>& a, bool runs, hipStream_t stream) {
+    if (runs) return launch_reduce<Chunks, T, kNB, kMaxWaves, false, true>(pl, a, stream);
+    return launch_reduce<Chunks, T, kNB, kMaxWaves, false, false>(pl, a, stream);
 }
 
 template <class Chunks, typename T>
@@ -1560,24 +1589,51 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
                          float* const* grad_shards, hipStream_t stream) {
     fsdp_status st = FSDP_OK;
     if (grad_shards == nullptr) return fail(FSDP_ERR_INVALID, "grad_shards is NULL");
-    constexpr int64_t tile = int64_t(kReduceBlock) * Unit<T>::kPer;
+    constexpr int64_t kWave = int64_t(kReduceBlock) * Unit<T>::kPer;   // outputs of one wave
     Spans outs;
-    int64_t nt = 0;
+    int64_t waves = 0, waves_off = 0;   // all waves, those whose sources are off the 128-byte lines
     bool any = !chunks_aligned(src);
+    const bool lines = chunks_on_lines(src, pl.world);
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t v = pl.local_elems(p, rank);
         if ((st = check_param_ptr(grad_shards[p], v, 4, p, "grad_shards")) != FSDP_OK) return st;
         if (v > 0) outs.add(grad_shards[p], v * 4);
-        nt += tiles(v, tile);
         // Sources of parameter p start at off_p in every chunk.
-        if (((pl.off[p] * int64_t(sizeof(T))) & 15) || !aligned16(grad_shards[p])) any = true;
+        const int64_t byte = pl.off[p] * int64_t(sizeof(T));
+        if ((byte & 15) || !aligned16(grad_shards[p])) any = true;
+        waves += tiles(v, kWave);
+        if (!lines || (byte & 127)) waves_off += tiles(v, kWave);
     }
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
-    if (nt == 0) return FSDP_OK;                         // nothing to write: no launch
-    if (nt > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
+    if (waves == 0) return FSDP_OK;                      // nothing to write: no launch
+    if (waves > INT32_MAX) return fail(FSDP_ERR_OVERFLOW, "too many work tiles");
     // (The first HIP call: every argument is checked.)
     const int cus = cu_count(&st);
     if (st != FSDP_OK) return st;
+    // The shard's waves per CU decide how many sources a wave keeps in flight
+    // (24-32 KB per CU, as far as the shard goes) and, where they are more than
+    // the CU holds, how many run at once.  Measured, kNB = 1 / 2 / 4: 8B block
+    // at W = 128 (13 waves per CU) 66.8 / 68.0 / 71.3 us; 0.95 M outputs at
+    // W = 64 (7 waves) 24.7 / 21.6 / 22.7; 64 norm shards at W = 32 (1 wave on
+    // every fourth CU) 7.9 / 5.8 / 4.8.  Resident waves per SIMD 3 / 4 / 5: 70B
+    // block, W = 64: 271 / 275 / 281; uneven bucket, W = 48: 384 / 390 / 401;
+    // 8B block, W = 8: 89.9 / 89.0 / 88.5.  Tiles off the grid are added batch
+    // by batch and want two sources: dense uneven bucket 437 us, 488 without a
+    // cap.
+    bool large = waves >= int64_t(kReduceCapWaves) * cus;
+    int batch = waves >= int64_t(kReduceOneWaves) * cus ? 1 : waves >= int64_t(kReduceTwoWaves) * cus ? 2 : 4;
+    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true, batch = 1;
+    if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) large = false, batch = 4;
+    const bool wide = pl.world >= kReduceWideW;
+    // Off the 128-byte lines two neighbouring tiles share a line of every source.
+    // In plain order they run on different dies, and each die's L2 fetches the
+    // line; so the tiles are dealt in runs, as the copies' are, where the sources
+    // of most of them are off the lines.  Five segments 16 bytes off the lines,
+    // 64 waves per CU, plain / runs: W = 8 31.8 / 29.2 us, W = 32 101 / 90 us;
+    // 16 waves per CU, W = 32: 30.0 / 24.6.  On the lines the 8B block at
+    // W = 128 takes 63.4 / 64.8, the uneven bucket 400 / 408.  (The form for the
+    // smallest shards has no such order: 8 runs are 8 waves per CU.)
+    const bool runs = 2 * waves_off > waves;
     // Tiles of the parameters with the fewest tiles are numbered (and so
     // dispatched) first: a ragged last tile sums its W sources in a longer
     // dependent chain, which then overlaps the bulk instead of trailing it.
@@ -1586,7 +1642,7 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     int order[PMAX];
     int64_t nts[PMAX];
     for (int p = 0; p < pl.nparams; ++p) {
-        nts[p] = tiles(pl.local_elems(p, rank), tile);
+        nts[p] = tiles(pl.local_elems(p, rank), kWave);
         int q = p;
         for (; q > 0 && nts[order[q - 1]] > nts[p]; --q) order[q] = order[q - 1];
         order[q] = p;
@@ -1602,30 +1658,17 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     finish_table(pl, &a.table);
     a.src = src;
     a.world = pl.world;
-    a.ntiles = uint32_t(nt);
-    // The shard's waves per CU decide how many sources a wave keeps in flight
-    // (24-32 KB per CU, as far as the shard goes) and, where they are more than
-    // the CU holds, how many run at once.  Measured, kNB = 1 / 2 / 4: 8B block
-    // at W = 128 (13 waves per CU) 66.8 / 68.0 / 71.3 us; 0.95 M outputs at
-    // W = 64 (7 waves) 24.7 / 21.6 / 22.7; 64 norm shards at W = 32 (1 wave on
-    // every fourth CU) 7.9 / 5.8 / 4.8.  Resident waves per SIMD 3 / 4 / 5: 70B
-    // block, W = 64: 271 / 275 / 281; uneven bucket, W = 48: 384 / 390 / 401;
-    // 8B block, W = 8: 89.9 / 89.0 / 88.5.  Tiles off the grid are added batch
-    // by batch and want two sources: dense uneven bucket 437 us, 488 without a
-    // cap.
-    bool large = nt >= int64_t(kReduceCapWaves) * cus;
-    int batch = nt >= int64_t(kReduceOneWaves) * cus ? 1 : nt >= int64_t(kReduceTwoWaves) * cus ? 2 : 4;
-    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true, batch = 1;
-    if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) large = false, batch = 4;
+    a.ntiles = uint32_t(t0);
     if (any) {
-        if (batch == 4) return launch_reduce<Chunks, T, 4, 8, true>(pl, a, stream);
-        return launch_reduce<Chunks, T, 2, kReduceWaves, true>(pl, a, stream);
+        if (batch == 4) return launch_reduce<Chunks, T, 4, 8, true, false>(pl, a, stream);
+        if (runs) return launch_reduce<Chunks, T, 2, kReduceWaves, true, true>(pl, a, stream);
+        return launch_reduce<Chunks, T, 2, kReduceWaves, true, false>(pl, a, stream);
     }
-    if (large && pl.world >= kReduceWideW) return launch_reduce<Chunks, T, 1, kReduceWaves - 1, false>(pl, a, stream);
-    if (large) return launch_reduce<Chunks, T, 1, kReduceWaves, false>(pl, a, stream);
-    if (batch == 1) return launch_reduce<Chunks, T, 1, 8, false>(pl, a, stream);
-    if (batch == 2) return launch_reduce<Chunks, T, 2, 8, false>(pl, a, stream);
-    return launch_reduce<Chunks, T, 4, 8, false>(pl, a, stream);
+    if (large && wide) return launch_reduce<Chunks, T, 1, kReduceWaves - 1>(pl, a, runs, stream);
+    if (large) return launch_reduce<Chunks, T, 1, kReduceWaves>(pl, a, runs, stream);
+    if (batch == 1) return launch_reduce<Chunks, T, 1, 8>(pl, a, runs, stream);
+    if (batch == 2) return launch_reduce<Chunks, T, 2, 8>(pl, a, runs, stream);
+    return launch_reduce<Chunks, T, 4, 8, false, false>(pl, a, stream);
 }
 
 }  // namespace

@@ -171,6 +171,24 @@ def test_reduce_forms(w, waves_per_cu, align):
     plan.close()
 
 
+@pytest.mark.parametrize("off", [0, 8])
+@pytest.mark.parametrize("w,waves_per_cu", [(2, 5), (5, 10), (9, 26), (9, 32), (33, 32)])
+def test_reduce_tile_order(w, waves_per_cu, off):
+    """One bucket buffer whose segments and chunks lie on the 128-byte lines,
+    and 16 bytes off them (where the tiles are dealt to the dies in runs): the
+    whole grid at once, and few workgroups that loop over it."""
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    n = waves_per_cu * cus * 512
+    dims = [(w * off, 1), (w * n + 1 - w, 1), (w * (64 + off), 1)]
+    oplan = O.make_plan(w, dims, 8)
+    assert all(o % 64 == (off if p else 0) for p, o in enumerate(oplan.offset)) and oplan.chunk % 64 == off * 2
+    recv = wide_bf16_host([w, waves_per_cu, off], w * oplan.chunk)
+    for cap in (0, 61):
+        plan = BucketPlan(w, dims, 8, max_workgroups=cap)
+        run_rs_reduce(plan, oplan, w - 1, recv)
+        plan.close()
+
+
 @pytest.mark.parametrize("align", [8, 1])
 @pytest.mark.parametrize("shift", [0, 1, 9, 33])
 def test_copy_lines(align, shift):

@@ -245,6 +245,47 @@ def test_push_grid_stride(cap):
     test_ag_pack_push(4, max_workgroups=cap)
 
 
+# (W, waves per CU of the bulk, reduce_tiles): every form of the reduction, W on
+# both sides of its batches.
+REDUCE_FORMS = [(2, 1, "auto"), (2, 5, "auto"), (5, 7, "auto"), (3, 10, "auto"), (9, 12, "auto"), (5, 2, "full"),
+                (8, 3, "full"), (33, 1, "full")]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("start", [0, 8, 1])
+def test_reduce_forms_loop_over_tiles(dtype, start):
+    """Every form of the reduction with one tile per workgroup and with few
+    workgroups that loop over the tiles of several parameters, from W chunk
+    tensors; the bulk on the 128-byte lines, off them (start 8) and off the
+    16-byte grid (start 1), with ragged ends."""
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    for W, waves, tiles in REDUCE_FORMS:
+        n = waves * cus * (256 if dtype == "f32" else 512)
+        dims = [(start * W, 1), (n * W + 1 - W, 1), (W * 77, 1), (3 * W + 1, 5)]
+        align = 8 if start != 1 else 1
+        oplan = O.make_plan(W, dims, align)
+        S = oplan.chunk
+        if dtype == "f32":
+            recv = _wide_f32([W, waves, start], W * S)
+        else:
+            recv = random_bits16([W, waves, start], W * S)
+            recv = (recv & 0xBFFF).view(np.float16) if dtype == "f16" else recv & 0xBFFF      # finite
+        chunks = _chunks(W, S, dtype, recv)
+        r = W - 1                                                # holds fewer elements of the bulk
+        want = O.rs_reduce(oplan, r, recv)
+        for cap in (0, 7, 50):
+            plan = BucketPlan(W, dims, align, max_workgroups=cap, reduce_tiles=tiles)
+            for shift in (0, 4) if start == 0 and cap != 7 else (0,):      # outputs off the lines
+                outs = [Guarded(O.local_elems(oplan, p, r), torch.float32, shift) for p in range(len(dims))]
+                step(f"rs_reduce_ex {dtype} W={W} waves={waves} {tiles} start={start} cap={cap} shift={shift}")
+                plan.rs_reduce_ex(r, [c.view for c in chunks], [o.view for o in outs], dtype)
+                torch.cuda.synchronize()
+                for p, o in enumerate(outs):
+                    assert o.guards_intact(), p
+                    assert np.array_equal(host_u32(o.view), want[p].reshape(-1).view(np.uint32)), p
+            plan.close()
+
+
 def test_ex_chunks_alias_one_buffer():
     """The chunk table may point into one [W][S] buffer: the results equal the
     contiguous calls bit for bit."""

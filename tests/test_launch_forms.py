@@ -13,6 +13,10 @@ import sys
 
 import pytest
 
+import bench
+from paper_2411_00284_amd import BucketPlan
+from synth import WORKLOADS
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(os.path.dirname(HERE), "paper_2411_00284_amd", "libfsdp_bucket.so")
 CUS = 256
@@ -62,16 +66,42 @@ def test_forced_reduce_form_off_the_grid(launches, why, tiles, form):
     """A small shard off the grid: reduce_tiles="full" forces the form for
     large shards there too."""
     got, _ = launches([{"call": "rs_reduce", "world": 4, "tiles": tiles, **OFF_GRID[why]}])
-    assert got == [[f"rs_reduce_kernel<ContigChunks, unsigned short, {form}>"]]
+    runs = "true" if tiles == "full" and why != "output" else "false"
+    assert got == [[f"rs_reduce_kernel<ContigChunks, unsigned short, {form}, {runs}>"]]
 
 
-@pytest.mark.parametrize("tiles,form", [("full", "1, 4, false"), ("half", "4, 8, false"), ("auto", "4, 8, false")])
+@pytest.mark.parametrize("tiles,form", [("full", "1, 4, false, false"), ("half", "4, 8, false, false"),
+                                        ("auto", "4, 8, false, false")])
 def test_forced_reduce_form(launches, tiles, form):
     got, _ = launches([{"call": "rs_reduce", "world": 4, "tiles": tiles, "dims": [[64, 64]]},
                        {"call": "rs_reduce", "world": 4, "tiles": tiles, "dims": shard_of(4, 64 * CUS)}])
     assert got[0] == [f"rs_reduce_kernel<ContigChunks, unsigned short, {form}>"]
     if tiles != "auto":
         assert got[1] == got[0]
+
+
+def reduce_call(world, waves, wire="bf16", off=0, **more):
+    """A reduction of `waves` waves per CU of five parameters whose segments
+    start `off` elements past a 128-byte line."""
+    n = waves * CUS * (256 if wire == "f32" else 512) // 5 // 64 * 64
+    return {"call": "rs_reduce_ex" if more else "rs_reduce", "world": world, "wire": wire,
+            "dims": [[off * world, 1]] * (off > 0) + [[n * world, 1]] * 5, **more}
+
+
+OFF_LINES = {"segments": {"off": 8}, "chunks": {"chunk_shift": 16}, "f32 chunks": {"chunk_shift": 64, "wire": "f32"}}
+
+
+@pytest.mark.parametrize("why", OFF_LINES)
+@pytest.mark.parametrize("world,waves,form", [(8, 7, "2, 8"), (8, 20, "1, 8"), (8, 40, "1, 4"), (48, 20, "1, 8"),
+                                              (48, 100, "1, 3")])
+def test_reduce_off_the_lines_in_runs(launches, why, world, waves, form):
+    """Where the sources of most tiles are off the 128-byte lines, the tiles are
+    dealt to the dies in runs; a few such tiles, or outputs there, change nothing."""
+    few = reduce_call(world, waves)
+    few["dims"] = few["dims"] + [[8 * world, 1], [56 * world, 1]]  # the chunks stay on the lines
+    got, _ = launches([reduce_call(world, waves, **OFF_LINES[why]), few, reduce_call(world, waves, shift=64)])
+    plain = [*form.split(", "), "false", "false>"]
+    assert [n[0].rsplit(", ", 4)[1:] for n in got] == [[*form.split(", "), "false", "true>"], plain, plain]
 
 
 def every_form():
@@ -92,8 +122,9 @@ def every_form():
     reduces = [("rs_reduce", "bf16"), ("rs_reduce_ex", "bf16"), ("rs_reduce_ex", "f16"), ("rs_reduce_ex", "f32")]
     for world, waves, (call, wire) in itertools.product((2, 8, 40), (1, 7, 20, 40, 70, 100), reduces):
         dims = shard_of(world, waves * CUS, 256 if wire == "f32" else 512)
-        calls += [{"call": call, "world": world, "wire": wire, "dims": dims},
-                  {"call": call, "world": world, "wire": wire, "dims": [[9, 1], *dims], "align": 1}]
+        calls += [{"call": call, "world": world, "wire": wire, "dims": d, "align": align}
+                  for d, align in ((dims, 8), ([[8 * world, 1], *dims], 8), ([[9, 1], *dims], 1))]
+        calls.append({"call": call, "world": world, "wire": wire, "dims": dims, "shift": 4})
     return calls
 
 
@@ -102,3 +133,19 @@ def test_every_kernel_is_reached(launches):
     launched, kernels = launches(every_form())
     assert all(launched)
     assert sorted(set(kernels) - {k for names in launched for k in names}) == []
+
+
+@pytest.mark.parametrize("align", [8, 1])
+def test_the_benchmark_names_the_kernels(launches, align):
+    """The symbols that the benchmark gives for a call without a trace are the
+    kernels that the library launches."""
+    calls, names = [], []
+    for wl in WORKLOADS.values():
+        plan = BucketPlan(wl.world_size, wl.dims, align)
+        for name, rank in itertools.product(bench.KERNELS, sorted({0, wl.world_size // 2, wl.world_size - 1})):
+            if any(plan.local_elems(p, rank) for p in range(plan.num_params)):
+                calls.append({"call": name, "world": wl.world_size, "dims": [list(d) for d in wl.dims], "rank": rank,
+                              "align": align})
+                names.append([bench.kernel_symbol(name, plan, rank, CUS)])
+        plan.close()
+    assert launches(calls)[0] == names

@@ -45,7 +45,7 @@ namespace {
 #define FSDP_REDUCE_WAVES 4
 #endif
 #ifndef FSDP_REDUCE_CAP_WAVES
-#define FSDP_REDUCE_CAP_WAVES 32
+#define FSDP_REDUCE_CAP_WAVES 26
 #endif
 #ifndef FSDP_REDUCE_ONE_WAVES
 #define FSDP_REDUCE_ONE_WAVES 10
@@ -76,10 +76,13 @@ static_assert(kCopyBlock % 64 == 0 && kWidenBlock % 64 == 0 && kPackBlock % 64 =
               "workgroups are whole wavefronts, the reduction's one wavefront");
 constexpr int kReduceWaves = FSDP_REDUCE_WAVES;           // resident waves per SIMD of a large shard's reduction
 constexpr int kReduceCapWaves = FSDP_REDUCE_CAP_WAVES;    // waves per CU from which a shard is large
-constexpr int kReduceWideW = 32;                          // ... and W from which one wave fewer is resident
+constexpr int kReduceFewW = 7;                            // ... and W up to which none is capped
+constexpr int kReduceWideW = 32;                          // ... and W from which one wave fewer is resident,
+constexpr int kReduceWideWaves = 32;                      // ... in a shard of as many waves per CU,
+constexpr int kReducePlainWaves = 96;                     // ... and tiles on the lines are in plain order from here
 constexpr int kReduceOneWaves = FSDP_REDUCE_ONE_WAVES;    // ... from which a wave keeps one source in flight, not two
 constexpr int kReduceTwoWaves = FSDP_REDUCE_TWO_WAVES;    // ... two sources, not four
-constexpr int kReduceFewW = 4;                            // sources up to which fp32 outputs always write through
+constexpr int kReduceThroughW = 4;                        // W up to which an fp32 wire's averages always write through
 constexpr int kBlocksPerCU = FSDP_BLOCKS_PER_CU;  // workgroups per CU in the grid-stride launch
 constexpr int kXcds = 8;                          // accelerator dies; workgroup b runs on die b % 8
 constexpr int kXcdRun = FSDP_XCD_RUN;             // consecutive copy tiles dealt to one die
@@ -1139,7 +1142,7 @@ __device__ __forceinline__ void store_units(float* tile, uint32_t units, const f
 // better for them not to wait in the L2: W = 2, 17.1 us against 18.5.
 template <typename T>
 __device__ __forceinline__ bool store_through(const float* out, int W) {
-    return on_line(out) || (Unit<T>::kPer == 4 && W <= kReduceFewW);
+    return on_line(out) || (Unit<T>::kPer == 4 && W <= kReduceThroughW);
 }
 
 // A tile of a reduction: elements [first, first + n) of every chunk, n <= kElems.
@@ -1611,29 +1614,38 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     const int cus = cu_count(&st);
     if (st != FSDP_OK) return st;
     // The shard's waves per CU decide how many sources a wave keeps in flight
-    // (24-32 KB per CU, as far as the shard goes) and, where they are more than
-    // the CU holds, how many run at once.  Measured, kNB = 1 / 2 / 4: 8B block
-    // at W = 128 (13 waves per CU) 66.8 / 68.0 / 71.3 us; 0.95 M outputs at
-    // W = 64 (7 waves) 24.7 / 21.6 / 22.7; 64 norm shards at W = 32 (1 wave on
-    // every fourth CU) 7.9 / 5.8 / 4.8.  Resident waves per SIMD 3 / 4 / 5: 70B
-    // block, W = 64: 271 / 275 / 281; uneven bucket, W = 48: 384 / 390 / 401;
-    // 8B block, W = 8: 89.9 / 89.0 / 88.5.  Tiles off the grid are added batch
-    // by batch and want two sources: dense uneven bucket 437 us, 488 without a
-    // cap.
-    bool large = waves >= int64_t(kReduceCapWaves) * cus;
-    int batch = waves >= int64_t(kReduceOneWaves) * cus ? 1 : waves >= int64_t(kReduceTwoWaves) * cus ? 2 : 4;
-    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true, batch = 1;
-    if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) large = false, batch = 4;
-    const bool wide = pl.world >= kReduceWideW;
+    // (24-32 KB per CU, as far as the shard goes).  Measured, kNB = 1 / 2 / 4:
+    // 8B block at W = 128 (13 waves per CU) 66.8 / 68.0 / 71.3 us; 0.95 M outputs
+    // at W = 64 (7 waves) 24.7 / 21.6 / 22.7; 64 norm shards at W = 32 (1 wave on
+    // every fourth CU) 7.9 / 5.8 / 4.8.  Tiles off the grid are added batch by
+    // batch and want two sources: dense uneven bucket 437 us, 488 without a cap.
+    //
+    // Where the waves are more than stream well together, how many are resident
+    // per SIMD.  3 / 4 / 8: 70B block, W = 64: 262 / 274 / 283; uneven bucket,
+    // W = 48: 404 / 416 / 436; 8B block, W = 8: 88 / 87 / 89; five segments on
+    // the lines, W = 16, 31 waves per CU: 26.5 / 24.8 / 26.8, 64 waves: 49.5 / 46.3
+    // / 49.5.  A wave of few sources is not long in its stream, and needs the
+    // others beside it: W = 3, 64 waves per CU 19.8 / 18.1 / 16.8.
+    const auto from = [&](int per_cu) { return waves >= int64_t(per_cu) * cus; };
+    bool large = from(kReduceCapWaves), wide = pl.world >= kReduceWideW && from(kReduceWideWaves);
+    int batch = from(kReduceOneWaves) ? 1 : from(kReduceTwoWaves) ? 2 : 4;
+    if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true, wide = pl.world >= kReduceWideW, batch = 1;
+    if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) large = wide = false, batch = 4;
     // Off the 128-byte lines two neighbouring tiles share a line of every source.
     // In plain order they run on different dies, and each die's L2 fetches the
     // line; so the tiles are dealt in runs, as the copies' are, where the sources
     // of most of them are off the lines.  Five segments 16 bytes off the lines,
     // 64 waves per CU, plain / runs: W = 8 31.8 / 29.2 us, W = 32 101 / 90 us;
-    // 16 waves per CU, W = 32: 30.0 / 24.6.  On the lines the 8B block at
-    // W = 128 takes 63.4 / 64.8, the uneven bucket 400 / 408.  (The form for the
-    // smallest shards has no such order: 8 runs are 8 waves per CU.)
-    const bool runs = 2 * waves_off > waves;
+    // 16 waves per CU, W = 32: 30.0 / 24.6.  (The form for the smallest shards
+    // has no such order: 8 runs are 8 waves per CU.)
+    //
+    // On the lines runs are better where a shard takes a few rounds of resident
+    // waves (W = 64, 40 waves per CU: 117 / 107; W = 8, 36 waves: 19.6 / 18.4)
+    // and, of fewer sources, beyond (70B block's TP-8 shards, W = 8: 45.6 / 44.3),
+    // no better where all of it is resident (8B block, W = 128: 63.4 / 64.8) or W
+    // is large and the shard too (70B block 262 / 264, uneven bucket 400 / 408).
+    const bool off = 2 * waves_off > waves;
+    const bool runs = off || (large && !(wide && from(kReducePlainWaves)));
     // Tiles of the parameters with the fewest tiles are numbered (and so
     // dispatched) first: a ragged last tile sums its W sources in a longer
     // dependent chain, which then overlaps the bulk instead of trailing it.
@@ -1661,11 +1673,11 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     a.ntiles = uint32_t(t0);
     if (any) {
         if (batch == 4) return launch_reduce<Chunks, T, 4, 8, true, false>(pl, a, stream);
-        if (runs) return launch_reduce<Chunks, T, 2, kReduceWaves, true, true>(pl, a, stream);
+        if (off) return launch_reduce<Chunks, T, 2, kReduceWaves, true, true>(pl, a, stream);
         return launch_reduce<Chunks, T, 2, kReduceWaves, true, false>(pl, a, stream);
     }
-    if (large && wide) return launch_reduce<Chunks, T, 1, kReduceWaves - 1>(pl, a, runs, stream);
-    if (large) return launch_reduce<Chunks, T, 1, kReduceWaves>(pl, a, runs, stream);
+    if (wide) return launch_reduce<Chunks, T, 1, kReduceWaves - 1>(pl, a, runs, stream);
+    if (large && pl.world > kReduceFewW) return launch_reduce<Chunks, T, 1, kReduceWaves, false, true>(pl, a, stream);
     if (batch == 1) return launch_reduce<Chunks, T, 1, 8>(pl, a, runs, stream);
     if (batch == 2) return launch_reduce<Chunks, T, 2, 8>(pl, a, runs, stream);
     return launch_reduce<Chunks, T, 4, 8, false, false>(pl, a, stream);

@@ -70,14 +70,31 @@ def test_forced_reduce_form_off_the_grid(launches, why, tiles, form):
     assert got == [[f"rs_reduce_kernel<ContigChunks, unsigned short, {form}, {runs}>"]]
 
 
-@pytest.mark.parametrize("tiles,form", [("full", "1, 4, false, false"), ("half", "4, 8, false, false"),
-                                        ("auto", "4, 8, false, false")])
-def test_forced_reduce_form(launches, tiles, form):
-    got, _ = launches([{"call": "rs_reduce", "world": 4, "tiles": tiles, "dims": [[64, 64]]},
-                       {"call": "rs_reduce", "world": 4, "tiles": tiles, "dims": shard_of(4, 64 * CUS)}])
-    assert got[0] == [f"rs_reduce_kernel<ContigChunks, unsigned short, {form}>"]
-    if tiles != "auto":
-        assert got[1] == got[0]
+@pytest.mark.parametrize("world,form", [(4, "1, 8, false, true"), (8, "1, 4, false, true"), (32, "1, 3, false, true")])
+@pytest.mark.parametrize("tiles", ["full", "half", "auto"])
+def test_forced_reduce_form(launches, tiles, world, form):
+    small = "4, 8, false, false"
+    got, _ = launches([{"call": "rs_reduce", "world": world, "tiles": tiles, "dims": [[world * 64, 64]]},
+                       {"call": "rs_reduce", "world": world, "tiles": tiles, "dims": shard_of(world, 64 * CUS)}])
+    want = {"full": [form, form], "half": [small, small], "auto": [small, form]}[tiles]
+    assert got == [[f"rs_reduce_kernel<ContigChunks, unsigned short, {f}>"] for f in want]
+
+
+@pytest.mark.parametrize("world,forms", [
+    (1, {4: "4, 8, false", 5: "2, 8, false", 10: "1, 8, false", 25: "1, 8, false", 26: "1, 8, true",
+         200: "1, 8, true"}),
+    (7, {9: "2, 8, false", 10: "1, 8, false", 25: "1, 8, false", 26: "1, 8, true", 200: "1, 8, true"}),
+    (8, {9: "2, 8, false", 10: "1, 8, false", 25: "1, 8, false", 26: "1, 4, true", 200: "1, 4, true"}),
+    (31, {25: "1, 8, false", 26: "1, 4, true", 200: "1, 4, true"}),
+    (32, {25: "1, 8, false", 26: "1, 4, true", 31: "1, 4, true", 32: "1, 3, true", 95: "1, 3, true", 96: "1, 3, false"}),
+    (128, {31: "1, 4, true", 32: "1, 3, true", 96: "1, 3, false", 200: "1, 3, false"}),
+])
+def test_reduce_form_by_size(launches, world, forms):
+    """Resident waves and tile order of a shard on the lines, on both sides of
+    every bound; "sources in flight, resident waves, in runs"."""
+    got, _ = launches([{"call": "rs_reduce", "world": world, "dims": shard_of(world, w * CUS)} for w in forms])
+    want = [[n, m, "false", runs] for n, m, runs in (f.split(", ") for f in forms.values())]
+    assert [g[0].rstrip(">").rsplit(", ", 4)[1:] for g in got] == want
 
 
 def reduce_call(world, waves, wire="bf16", off=0, **more):
@@ -92,8 +109,7 @@ OFF_LINES = {"segments": {"off": 8}, "chunks": {"chunk_shift": 16}, "f32 chunks"
 
 
 @pytest.mark.parametrize("why", OFF_LINES)
-@pytest.mark.parametrize("world,waves,form", [(8, 7, "2, 8"), (8, 20, "1, 8"), (8, 40, "1, 4"), (48, 20, "1, 8"),
-                                              (48, 100, "1, 3")])
+@pytest.mark.parametrize("world,waves,form", [(8, 7, "2, 8"), (8, 20, "1, 8"), (48, 20, "1, 8"), (48, 100, "1, 3")])
 def test_reduce_off_the_lines_in_runs(launches, why, world, waves, form):
     """Where the sources of most tiles are off the 128-byte lines, the tiles are
     dealt to the dies in runs; a few such tiles, or outputs there, change nothing."""

@@ -80,6 +80,7 @@ REDUCE_WIDE_W, REDUCE_WIDE_WAVES, REDUCE_PLAIN_WAVES = 32, 32, 96
 PACK_BIG_TILE = 256 * 8 * 4
 PACK_SMALL_TILE = 128 * 8
 PACK_BIG_TILES_PER_CU = 4
+COPY_TILE, COPY_LINE_TILES_PER_CU = 128 * 8 * 2, 44
 
 
 def algorithmic_bytes(W, S, E, V0):
@@ -116,11 +117,13 @@ def kernel_symbol(name, plan, rank, cus):
     P, S = plan.num_params, plan.chunk_elems
     offsets, segs = [2 * plan.offset(p) for p in range(P)], [2 * plan.seg_elems(p) for p in range(P)]
     if name == "ag_unpack":                                  # chunks are read, parameters written
-        off_grid = any(o % 16 for o in [2 * S] + offsets) or any(n % 128 for n in segs)
-        return KERNEL_SYMBOLS[name].replace("false>", "true>") if off_grid else KERNEL_SYMBOLS[name]
+        written, tiles = segs, sum(-(-n // (2 * COPY_TILE)) for n in segs)
     if name == "rs_pack":                                    # gradients are read, chunks written
-        off_grid = any(n % 16 for n in segs) or any(o % 128 for o in [2 * S] + offsets)
-        return KERNEL_SYMBOLS[name].replace("false>", "true>") if off_grid else KERNEL_SYMBOLS[name]
+        written, tiles = [2 * S] + offsets, pack_tiles(plan, COPY_TILE)
+    if name in ("ag_unpack", "rs_pack"):
+        large = plan.world_size * tiles >= COPY_LINE_TILES_PER_CU * cus
+        any_form = any(n % 16 for n in [2 * S] + offsets + segs) or (large and any(n % 128 for n in written))
+        return KERNEL_SYMBOLS[name].replace("false>", "true>") if any_form else KERNEL_SYMBOLS[name]
     if name == "rs_reduce":
         waves = [-(-plan.local_elems(p, rank) // REDUCE_TILE) for p in range(P)]
         off = sum(w for w, o in zip(waves, offsets) if o % 128 or 2 * S % 128)

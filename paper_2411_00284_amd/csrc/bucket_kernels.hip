@@ -379,9 +379,9 @@ __device__ __forceinline__ void seg_copy_any(const uint16_t* __restrict__ s, uin
     }
 }
 
-// kAny: the launch has segments that start off the 16-byte grid or are written
-// off the 128-byte lines; those take seg_copy_any (the host picks kAny only
-// when there are some, so that the aligned kernels keep their own code).
+// kAny: the launch has segments that start off the 16-byte grid, or in a large
+// bucket are written off the 128-byte lines; those take seg_copy_any (the host
+// picks kAny only then, so that the aligned kernels keep their own code).
 // (vs, e): the segment's valid elements and its end, for seg_copy_any, whose
 // lines may run past hi.
 template <int kSteps, bool kAny>
@@ -1505,9 +1505,35 @@ bool chunks_on_lines(const TableChunks& c, int world) {
     for (int i = 0; i < world; ++i) all |= uintptr_t(c.ptr[i]);
     return (all & 127) == 0;
 }
-// Whether some segment is read off the 16-byte grid or written off the lines:
-// (read, written) are the alignments in bytes of a segment's start and length.
-bool off_grid(int64_t read, int64_t written) { return (read & 15) != 0 || (written & 127) != 0; }
+// What a copy's segments are off: the 16-byte grid (read or written), or the
+// 128-byte lines (written).
+struct Off {
+    bool grid, lines;
+    // (read, written): the alignments in bytes of a segment's start and length.
+    void add(int64_t read, int64_t written) {
+        if (((read | written) & 15) != 0) grid = true;
+        if ((written & 127) != 0) lines = true;
+    }
+};
+
+// Whether a launch of `ntiles` copy tiles takes the any-address kernel: if some
+// segment is off the grid, and, if one is written off the lines, from
+// kCopyLineTilesPerCU tiles per CU on.  A large bucket pays for the lines that two
+// tiles share; a small one for the longer way to a tile's first store.
+// Line-following / aligned kernel, W = 32, all segments 16 bytes off the lines,
+// MB over all ranks: rs_pack of 2 MB 4.8 / 3.6 us, 12 MB 7.7 / 7.1, 40 MB (38 tiles
+// per CU) 16.6 / 16.0, 60 MB 21.8 / 22.4, 600 MB 182 / 202; ag_unpack of 2 MB 4.6 /
+// 3.6, 12 MB 7.5 / 7.1, 40 MB 16.3 / 16.1, 60 MB 21.9 / 22.7, 600 MB 183 / 200.
+constexpr int kCopyLineTilesPerCU = 44;
+
+fsdp_status copy_takes_any(const Off& off, int64_t ntiles, bool* any) {
+    *any = off.grid;
+    if (off.grid || !off.lines || ntiles == 0) return FSDP_OK;
+    fsdp_status st = FSDP_OK;
+    const int cus = cu_count(&st);
+    *any = ntiles >= int64_t(kCopyLineTilesPerCU) * cus;
+    return st;
+}
 
 // ---- ag_unpack
 
@@ -1519,7 +1545,7 @@ fsdp_status do_ag_unpack(const Plan& pl, const Chunks& src, const Spans& ins, in
     UnpackArgs<Chunks> a{};
     Spans outs;
     int64_t nt = 0;               // tiles of one chunk
-    bool any = !chunks_aligned(src);
+    Off off{!chunks_aligned(src), false};
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t e = pl.elems[p];
         if ((st = check_param_ptr(params[p], e, 2 * u, p, "params")) != FSDP_OK) return st;
@@ -1527,12 +1553,14 @@ fsdp_status do_ag_unpack(const Plan& pl, const Chunks& src, const Spans& ins, in
         if ((st = add_copy_tiles(pl, p, tiles(pl.seg[p] * u, kCopyTile), &a.tiles, &nt)) != FSDP_OK) return st;
         // Segment i of parameter p is read from chunk i at off_p and written
         // to params[p] at i * L_p.
-        if (off_grid(a.param[p].off * 2, (a.param[p].seg * 2) | int64_t(uintptr_t(params[p])))) any = true;
+        off.add(a.param[p].off * 2, (a.param[p].seg * 2) | int64_t(uintptr_t(params[p])));
         if (e > 0) outs.add(params[p], e * 2 * u);
     }
     a.src = src;
     finish_copy_tiles(pl, nt, &a.tiles);
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
+    bool any;
+    if ((st = copy_takes_any(off, a.tiles.ntiles, &any)) != FSDP_OK) return st;
     if (any) return launch(pl, ag_unpack_kernel<Chunks, true>, a, int(a.tiles.ntiles), kCopyBlock, stream);
     return launch(pl, ag_unpack_kernel<Chunks, false>, a, int(a.tiles.ntiles), kCopyBlock, stream);
 }
@@ -1551,7 +1579,7 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
     RsPackArgs<Chunks> a{};
     Spans ins;
     int64_t nt = 0;               // tiles of one chunk
-    bool any = !chunks_on_lines(dst, pl.world);
+    Off off{!chunks_aligned(dst), !chunks_on_lines(dst, pl.world)};
     for (int p = 0; p < pl.nparams; ++p) {
         const int64_t e = pl.elems[p];
         if ((st = check_param_ptr(grads[p], e, gsize, p, "grads")) != FSDP_OK) return st;
@@ -1560,7 +1588,7 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
         if ((st = add_copy_tiles(pl, p, n, &a.tiles, &nt)) != FSDP_OK) return st;
         // Segment j of parameter p is read from grads[p] at j * L_p and written
         // to chunk j at off_p.
-        if (off_grid((a.param[p].seg * 2) | int64_t(uintptr_t(grads[p])), a.param[p].off * 2)) any = true;
+        off.add((a.param[p].seg * 2) | int64_t(uintptr_t(grads[p])), a.param[p].off * 2);
         if (e > 0) ins.add(grads[p], e * gsize);
     }
     a.param[pl.nparams].off = pl.chunk * u;
@@ -1569,6 +1597,8 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
     // (The widening pack takes any address in its one form: seg_widen chooses tile by tile.)
     if constexpr (kWiden == kF32) {
+        bool any;
+        if ((st = copy_takes_any(off, a.tiles.ntiles, &any)) != FSDP_OK) return st;
         if (any) return launch(pl, rs_pack_kernel<Chunks, kWiden, true>, a, int(a.tiles.ntiles), kBlock, stream);
     }
     return launch(pl, rs_pack_kernel<Chunks, kWiden, false>, a, int(a.tiles.ntiles), kBlock, stream);

@@ -205,6 +205,25 @@ def test_copy_lines(align, shift):
     plan.close()
 
 
+@pytest.mark.parametrize("tiles_per_cu", [43, 44])
+@pytest.mark.parametrize("shift", [0, 8])
+def test_copy_lines_by_size(tiles_per_cu, shift):
+    """Buckets on the 16-byte grid and off the 128-byte lines, on both sides of
+    the size from which the copies follow the lines: segments shorter than a
+    line, ragged at every parameter's and the last rank's end."""
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    w, tile = 8, 128 * 8 * 2
+    few = [(w * 8, 1), (w * 56 - 3, 1), (5, 72), (w * 2056, 1)]
+    n = tiles_per_cu * cus // w - 5                  # whole tiles of a rank; the few have 5
+    dims = [*few, (w * n * tile - 7, 1)]
+    plan = BucketPlan(w, dims)
+    oplan = O.make_plan(w, dims)
+    assert sum(-(-oplan.seg[p] // tile) for p in range(5)) * w == tiles_per_cu * cus
+    run_ag_unpack(plan, oplan, seed=tiles_per_cu, shift=shift)
+    run_rs_pack(plan, oplan, seed=tiles_per_cu, shift=shift)
+    plan.close()
+
+
 @pytest.mark.parametrize("align,shift", [(8, 1), (1, 0), (1, 3)])
 def test_pack_big_tiles_off_the_grid(align, shift):
     """The single-chunk pack's big tiles with shards and segments off the

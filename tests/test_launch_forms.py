@@ -120,6 +120,20 @@ def test_reduce_off_the_lines_in_runs(launches, why, world, waves, form):
     assert [n[0].rsplit(", ", 4)[1:] for n in got] == [[*form.split(", "), "false", "true>"], plain, plain]
 
 
+@pytest.mark.parametrize("call", ["ag_unpack", "ag_unpack_ex", "rs_pack", "rs_pack_ex"])
+@pytest.mark.parametrize("first,align,any_from", [(2048, 8, None), (2040, 8, 44), (2047, 1, 0)])
+def test_copy_form_by_size(launches, call, first, align, any_from):
+    """On the 16-byte grid the form that follows the 128-byte lines is for large
+    buckets off the lines (44 tiles of 4 KB per CU); off the grid it is for all.
+    Segments of `first` elements, and of whole tiles after it."""
+    world, least = 8, (any_from or 0) * CUS // 8
+    tiles = [2, 44 * CUS // 8 - 1, 44 * CUS // 8, 200 * CUS // 8]           # of one chunk
+    # (the tables' chunks are on the lines whatever their length: only the second segment is off)
+    got, _ = launches([{"call": call, "world": world, "dims": [[world * first, 1], [world * (t - 1) * 2048, 1]],
+                        "align": align} for t in tiles])
+    assert [g[0].endswith("true>") for g in got] == [any_from is not None and t >= least for t in tiles]
+
+
 def every_form():
     """Calls that between them take every branch of the dispatch."""
     small, large = [[64, 64], [9, 64]], [[64, 64], [40_000_000, 1]]

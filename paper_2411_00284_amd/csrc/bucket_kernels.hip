@@ -401,11 +401,15 @@ __device__ __forceinline__ void seg_copy(const uint16_t* __restrict__ s, uint16_
 // the 16-byte grid through windows, otherwise from where they are.  Each
 // thread handles 4 elements per sub-step (8 bytes in, 16 bytes out), so that
 // every load and store instruction of a wave covers one contiguous run.
-template <int kSteps, int kFrom>
+// kAny: a tile off the 128-byte lines is not written through, which would send
+// its first and last line to memory in parts (the host picks it where those
+// count: kWidenLineTilesPerCU).
+template <int kSteps, int kFrom, bool kAny>
 __device__ __forceinline__ void seg_widen(const uint16_t* __restrict__ s, float* __restrict__ d, int64_t lo,
                                           int64_t hi, int64_t v) {
     const int n = int(hi - lo), nv = clamp_to(v - lo, n);
     const bool direct = is_aligned16(s) && is_aligned16(d);
+    const bool through = !kAny || on_line(d);          // a tile is a whole number of lines
     const char* const from = as_global(reinterpret_cast<const char*>(s + lo));
     char* const to = as_global(reinterpret_cast<char*>(d + lo));
     const auto cast = [](uint16_t x) { return widen_lo<kFrom>(x); };
@@ -430,7 +434,9 @@ __device__ __forceinline__ void seg_widen(const uint16_t* __restrict__ s, float*
         const f32x4 y = {widen_lo<kFrom>(x[u].x), widen_hi<kFrom>(x[u].x), widen_lo<kFrom>(x[u].y), widen_hi<kFrom>(x[u].y)};
         const bool mine = cut && ((i == nv / 4 && (nv & 3)) || (i == n / 4 && (n & 3)));
         if (direct) {
-            st16(out, mine ? ~0u : uint32_t(i) * 16, y);
+            const uint32_t byte = mine ? ~0u : uint32_t(i) * 16;
+            if (through) st16(out, byte, y);
+            else st16<kPolicyNt>(out, byte, __builtin_bit_cast(u32x4, y));
         } else if (!mine && i < n / 4) {
             __builtin_nontemporal_store(y, reinterpret_cast<f32x4_any4*>(to + uint32_t(i) * 16));
         }
@@ -953,7 +959,7 @@ rs_pack_kernel(const RsPackArgs<Chunks> a) {
         const uint16_t* s = q.data + int64_t(j) * q.seg;
         if constexpr (kWiden != kF32) {
             float* d = reinterpret_cast<float*>(a.dst.at(j)) + q.off;
-            seg_widen<kWidenSteps, kWiden>(s, d, lo, hi, v);
+            seg_widen<kWidenSteps, kWiden, kAny>(s, d, lo, hi, v);
         } else {
             uint16_t* d = reinterpret_cast<uint16_t*>(a.dst.at(j)) + q.off;
             seg_copy<kCopySteps, kAny>(s, d, lo, hi, v, v, region);
@@ -1525,13 +1531,19 @@ struct Off {
 // per CU) 16.6 / 16.0, 60 MB 21.8 / 22.4, 600 MB 182 / 202; ag_unpack of 2 MB 4.6 /
 // 3.6, 12 MB 7.5 / 7.1, 40 MB 16.3 / 16.1, 60 MB 21.9 / 22.7, 600 MB 183 / 200.
 constexpr int kCopyLineTilesPerCU = 44;
+// From here on the widening pack's tiles off the lines are not written through.  bf16 on an fp32 wire, segments off the lines
+// by 32 bytes, MB of fp32, written through / not: W = 1 30 MB 10.6 / 10.5 us, 100 MB
+// (95 tiles per CU) 27.1 / 26.3, 400 MB 101 / 95; W = 8 30 MB 10.5 / 10.8, 60 MB
+// 18.3 / 18.1, 100 MB 28.6 / 27.8, 400 MB 103 / 98; W = 32 20 MB 8.2 / 8.6, 100 MB
+// 27.8 / 27.7, 400 MB 105 / 98.
+constexpr int kWidenLineTilesPerCU = 96;
 
-fsdp_status copy_takes_any(const Off& off, int64_t ntiles, bool* any) {
+fsdp_status copy_takes_any(const Off& off, int64_t ntiles, int line_tiles_per_cu, bool* any) {
     *any = off.grid;
     if (off.grid || !off.lines || ntiles == 0) return FSDP_OK;
     fsdp_status st = FSDP_OK;
     const int cus = cu_count(&st);
-    *any = ntiles >= int64_t(kCopyLineTilesPerCU) * cus;
+    *any = ntiles >= int64_t(line_tiles_per_cu) * cus;
     return st;
 }
 
@@ -1560,7 +1572,7 @@ fsdp_status do_ag_unpack(const Plan& pl, const Chunks& src, const Spans& ins, in
     finish_copy_tiles(pl, nt, &a.tiles);
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
     bool any;
-    if ((st = copy_takes_any(off, a.tiles.ntiles, &any)) != FSDP_OK) return st;
+    if ((st = copy_takes_any(off, a.tiles.ntiles, kCopyLineTilesPerCU, &any)) != FSDP_OK) return st;
     if (any) return launch(pl, ag_unpack_kernel<Chunks, true>, a, int(a.tiles.ntiles), kCopyBlock, stream);
     return launch(pl, ag_unpack_kernel<Chunks, false>, a, int(a.tiles.ntiles), kCopyBlock, stream);
 }
@@ -1588,19 +1600,19 @@ fsdp_status do_rs_pack(const Plan& pl, const void* const* grads, int gsize, cons
         if ((st = add_copy_tiles(pl, p, n, &a.tiles, &nt)) != FSDP_OK) return st;
         // Segment j of parameter p is read from grads[p] at j * L_p and written
         // to chunk j at off_p.
-        off.add((a.param[p].seg * 2) | int64_t(uintptr_t(grads[p])), a.param[p].off * 2);
+        if (kWiden == kF32) off.add((a.param[p].seg * 2) | int64_t(uintptr_t(grads[p])), a.param[p].off * 2);
+        else off.add(0, pl.off[p] * 4);
         if (e > 0) ins.add(grads[p], e * gsize);
     }
     a.param[pl.nparams].off = pl.chunk * u;
     a.dst = dst;
     finish_copy_tiles(pl, nt, &a.tiles);
     if ((st = check_overlap(outs, ins)) != FSDP_OK) return st;
-    // (The widening pack takes any address in its one form: seg_widen chooses tile by tile.)
-    if constexpr (kWiden == kF32) {
-        bool any;
-        if ((st = copy_takes_any(off, a.tiles.ntiles, &any)) != FSDP_OK) return st;
-        if (any) return launch(pl, rs_pack_kernel<Chunks, kWiden, true>, a, int(a.tiles.ntiles), kBlock, stream);
-    }
+    if (kWiden != kF32) off.grid = false;              // the widening pack's one form takes any address
+    bool any;
+    if ((st = copy_takes_any(off, a.tiles.ntiles, kWiden == kF32 ? kCopyLineTilesPerCU : kWidenLineTilesPerCU, &any)) != FSDP_OK)
+        return st;
+    if (any) return launch(pl, rs_pack_kernel<Chunks, kWiden, true>, a, int(a.tiles.ntiles), kBlock, stream);
     return launch(pl, rs_pack_kernel<Chunks, kWiden, false>, a, int(a.tiles.ntiles), kBlock, stream);
 }
 

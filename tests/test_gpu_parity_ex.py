@@ -176,6 +176,37 @@ def test_ex_small(case, align, max_workgroups=0):
     plan.close()
 
 
+@pytest.mark.parametrize("tiles_per_cu", [95, 96])
+@pytest.mark.parametrize("grad,align,shift", [("bf16", 8, 0), ("bf16", 8, 8), ("f16", 1, 1)])
+def test_widening_pack_off_the_lines(grad, align, shift, tiles_per_cu):
+    """The widening pack on both sides of the size from which it does not write
+    through off the 128-byte lines: tiles on them and off them, on the 16-byte
+    grid and off it, ragged at every parameter's and the last rank's end."""
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    W, tile = 8, 256 * 4
+    n = tiles_per_cu * cus // W - 5                          # whole tiles of a rank; the other parameters have 5
+    dims = [(W * 32, 1), (W * 8, 1), (W * 56 - 3, 1), (W * 1032, 1), (W * n * tile - 7, 1)]
+    plan = BucketPlan(W, dims, align)
+    oplan = O.make_plan(W, dims, align)
+    S = oplan.chunk
+    assert sum(-(-s // tile) for s in oplan.seg) * W == tiles_per_cu * cus
+    grads = [random_bits16([tiles_per_cu, shift, p], a * b) for p, (a, b) in enumerate(dims)]
+    if grad == "f16":
+        grads = [g.view(np.float16) for g in grads]
+    bufs = [Guarded(g.size, TORCH[grad], shift) for g in grads]
+    for b, g in zip(bufs, grads):
+        b.view.copy_(_to_dev(g, grad))
+    chunks = _chunks(W, S, "f32")
+    step(f"rs_pack_ex {grad}->f32 off the lines, {tiles_per_cu} tiles per CU, align={align} shift={shift}")
+    plan.rs_pack_ex([b.view for b in bufs], [c.view for c in chunks], "f32")
+    torch.cuda.synchronize()
+    want = O.rs_pack(oplan, [g.reshape(d) for g, d in zip(grads, dims)], "f32")
+    for j, c in enumerate(chunks):
+        assert c.guards_intact(), j
+        assert _same(_host(c.view, "f32"), want[j * S:(j + 1) * S]), j
+    plan.close()
+
+
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_ag_pack_push(case, max_workgroups=0):
     """The packed chunk of one rank written to W separate destinations, bf16

@@ -134,6 +134,20 @@ def test_copy_form_by_size(launches, call, first, align, any_from):
     assert [g[0].endswith("true>") for g in got] == [any_from is not None and t >= least for t in tiles]
 
 
+@pytest.mark.parametrize("grad", ["bf16", "f16"])
+@pytest.mark.parametrize("first,align,shift", [(2048, 8, 0), (2040, 8, 0), (2047, 1, 0), (2048, 8, 64)])
+def test_widening_pack_form_by_size(launches, grad, first, align, shift):
+    """The widening pack does not write through off the 128-byte lines in buckets
+    of 96 tiles of 1024 elements per CU and more; the gradients' place changes nothing."""
+    world = 8
+    tiles = [4, 96 * CUS // world - 1, 96 * CUS // world, 200 * CUS // world]       # of one chunk
+    got, _ = launches([{"call": "rs_pack_ex", "world": world, "wire": "f32", "grad": grad, "align": align, "shift": shift,
+                        "dims": [[world * first, 1], [world * (t - 2) * 1024, 1]]} for t in tiles])
+    widen = {"bf16": 1, "f16": 2}[grad]
+    assert [g[0] for g in got] == [
+        f"rs_pack_kernel<TableChunks, {widen}, {'true' if first < 2048 and t >= tiles[2] else 'false'}>" for t in tiles]
+
+
 def every_form():
     """Calls that between them take every branch of the dispatch."""
     small, large = [[64, 64], [9, 64]], [[64, 64], [40_000_000, 1]]
@@ -146,7 +160,8 @@ def every_form():
             calls += [{"call": "rs_pack_ex", "world": 4, "dims": small, "wire": wire, **off},
                       {"call": "ag_unpack_ex", "world": 4, "dims": small, "wire": wire, **off}]
             if wire != "f32":
-                calls += [{"call": "rs_pack_ex", "world": 4, "dims": small, "wire": "f32", "grad": wire, **off}]
+                calls += [{"call": "rs_pack_ex", "world": 4, "dims": dims, "wire": "f32", "grad": wire, **off}
+                          for dims in (small, [[9, 1], [40_000_000, 1]])]
     calls += [{"call": c, "world": 4, "dims": small, **off}
               for c in ("ag_pack", "ag_unpack", "rs_pack") for off in ({}, odd)]
     reduces = [("rs_reduce", "bf16"), ("rs_reduce_ex", "bf16"), ("rs_reduce_ex", "f16"), ("rs_reduce_ex", "f32")]

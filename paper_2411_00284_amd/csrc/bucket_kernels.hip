@@ -802,7 +802,7 @@ __global__ void __launch_bounds__(kCopyBlock) replicate_grouped_kernel(const Rep
 // of one die (b, b + 8, b + 16, ...) take kXcdRun consecutive tiles, a 1 MB
 // run per die.  Against it, on the 8B, 70B and 405B blocks and the uneven
 // bucket: plain order 1-3 % slower, runs of 16 tiles 8 %, of 128, 512 and 1024
-// 0-3 %.  (The reduce takes it where its tiles share lines.)  The tiles past the
+// 0-3 %.  (The reduce takes it for some shards: see there.)  The tiles past the
 // last whole group keep order b.  A bijection on [0, n), so a grid-stride loop over
 // b still covers every tile once.
 __device__ __forceinline__ uint32_t copy_tile(uint32_t b, uint32_t n) {
@@ -842,7 +842,11 @@ Divider divider(uint32_t d) {
 //     many places meet in the memory controllers, and the copy is slower.
 // Both copies of the 70B block (3.42 GB): 530 -> 506 us unpack, 537 -> 512 us
 // pack (the look-up without the cap: 548 and 537; the cap without the look-up:
-// 531 and 532).  4 and 6 waves are 0-2 % slower, 3 waves 5 %, 8 waves 4-7 %.
+// 531 and 532).  3 waves are 5 % slower, 8 waves 4-7 %; 4 / 5 / 6, contiguous
+// buckets: 405B block's unpack 1887 / 1911 / 1920, its pack 1883 / 1885 / 1905;
+// 70B 507 / 511 / 517 and 501 / 502 / 509; 8B at W = 8 131.4 / 130.0 / 131.4 and
+// 129.7 / 129.0 / 130.5; 70B TP-8 shards 66.0 / 65.0 / 66.3 and 64.7 / 63.7 / 65.0:
+// 4 for the largest unpacks, 5 elsewhere.
 #ifndef FSDP_COPY_WAVES
 #define FSDP_COPY_WAVES 5
 #endif
@@ -850,7 +854,10 @@ constexpr int kCopyWaves = FSDP_COPY_WAVES;       // resident waves per SIMD
 #ifndef FSDP_COPY_ANY_WAVES
 #define FSDP_COPY_ANY_WAVES 6
 #endif
-constexpr int kCopyAnyWaves = FSDP_COPY_ANY_WAVES;   // ... where some segment is off the grid
+// ... where some tiles take seg_copy_any, whose addresses take longer: 4 / 5 / 6 /
+// 8 waves, uneven bucket, A = 1: unpack 880 / 792 / 771 / 781 us, pack 920 / 810 / 769
+// / 771; 30 MB, W = 8, A = 1: unpack 14.9 / 13.6 / 13.1 / 13.3.
+constexpr int kCopyAnyWaves = FSDP_COPY_ANY_WAVES;
 // The widening pack has half the bytes in flight per wave: no cap.
 template <int kWiden, bool kAny> constexpr int kPackMinWaves = kWiden != kF32 ? 4 : kAny ? kCopyAnyWaves : kCopyWaves;
 template <int kWiden, bool kAny> constexpr int kPackMaxWaves = kWiden != kF32 ? 8 : kAny ? kCopyAnyWaves : kCopyWaves;
@@ -1172,7 +1179,7 @@ struct ReduceSpot {
 };
 
 // What bounds the reduction is HBM: W reads for one fp32 write.  As in the
-// copies, the bytes in flight decide the rate: 16-32 KB of loads per CU stream
+// copies, the bytes in flight decide the rate: 24-32 KB of loads per CU stream
 // best, and more make it slower again, because the reads of many places (and
 // the few writes among them) then meet in the memory controllers.  So a
 // workgroup is one wave with one unit per lane, kNB sources are in flight
@@ -1531,11 +1538,12 @@ struct Off {
 // per CU) 16.6 / 16.0, 60 MB 21.8 / 22.4, 600 MB 182 / 202; ag_unpack of 2 MB 4.6 /
 // 3.6, 12 MB 7.5 / 7.1, 40 MB 16.3 / 16.1, 60 MB 21.9 / 22.7, 600 MB 183 / 200.
 constexpr int kCopyLineTilesPerCU = 44;
-// From here on the widening pack's tiles off the lines are not written through.  bf16 on an fp32 wire, segments off the lines
-// by 32 bytes, MB of fp32, written through / not: W = 1 30 MB 10.6 / 10.5 us, 100 MB
-// (95 tiles per CU) 27.1 / 26.3, 400 MB 101 / 95; W = 8 30 MB 10.5 / 10.8, 60 MB
-// 18.3 / 18.1, 100 MB 28.6 / 27.8, 400 MB 103 / 98; W = 32 20 MB 8.2 / 8.6, 100 MB
-// 27.8 / 27.7, 400 MB 105 / 98.
+// From here on the widening pack's tiles off the lines are not written through.
+// bf16 on an fp32 wire, segments 32 bytes off the lines, MB of fp32 over all
+// ranks, written through / not: W = 1 30 MB 10.6 / 10.5 us, 100 MB (95 tiles per
+// CU) 27.1 / 26.3, 400 MB 101 / 95; W = 8 30 MB 10.5 / 10.8, 60 MB 18.3 / 18.1, 100
+// MB 28.6 / 27.8, 400 MB 103 / 98; W = 32 20 MB 8.2 / 8.6, 100 MB 27.8 / 27.7, 400 MB
+// 105 / 98.
 constexpr int kWidenLineTilesPerCU = 96;
 
 fsdp_status copy_takes_any(const Off& off, int64_t ntiles, int line_tiles_per_cu, bool* any) {
@@ -1659,8 +1667,12 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     // (24-32 KB per CU, as far as the shard goes).  Measured, kNB = 1 / 2 / 4:
     // 8B block at W = 128 (13 waves per CU) 66.8 / 68.0 / 71.3 us; 0.95 M outputs
     // at W = 64 (7 waves) 24.7 / 21.6 / 22.7; 64 norm shards at W = 32 (1 wave on
-    // every fourth CU) 7.9 / 5.8 / 4.8.  Tiles off the grid are added batch by
-    // batch and want two sources: dense uneven bucket 437 us, 488 without a cap.
+    // every fourth CU) 7.9 / 5.8 / 4.8.  Off the grid, where a batch is added before
+    // the next is loaded, never one source.  There, kNB = 2 with the cap / 4, bf16,
+    // W = 24: 3 waves per CU 11.5 / 9.4 us, 8 waves 14.3 / 15.0, 12 waves 16.1 / 17.1, 20
+    // waves 27.6 / 25.8, 64 waves 75 / 87; at 5 to 7 waves these bounds, which are
+    // the other form's, are not the best ones (6 waves 13.4 / 11.4).  Dense uneven
+    // bucket: two sources 437 us, 488 without the cap.
     //
     // Where the waves are more than stream well together, how many are resident
     // per SIMD.  3 / 4 / 8: 70B block, W = 64: 262 / 274 / 283; uneven bucket,

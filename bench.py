@@ -75,8 +75,9 @@ SLEEP_CYCLES = 50_000_000                # a device-side wait that lets the host
 # The reduce's tile (one wave), the big pack tile and the thresholds of the
 # library's choice between the forms of each.
 REDUCE_TILE = 64 * 8
-REDUCE_CAP_WAVES, REDUCE_ONE_WAVES, REDUCE_TWO_WAVES, REDUCE_FEW_W = 26, 10, 5, 7
-REDUCE_WIDE_W, REDUCE_WIDE_WAVES, REDUCE_PLAIN_WAVES = 32, 32, 96
+REDUCE_CAP_WAVES, REDUCE_ONE_WAVES, REDUCE_TWO_WAVES, REDUCE_FEWEST_W, REDUCE_FEW_W = 26, 10, 5, 3, 7
+REDUCE_SOME_W, REDUCE_SOME_WAVES, REDUCE_PLAIN_WAVES = 11, 32, 192
+REDUCE_WIDE_W, REDUCE_WIDE_WAVES, REDUCE_WIDE_PLAIN_WAVES = 32, 32, 96
 PACK_BIG_TILE = 256 * 8 * 4
 PACK_SMALL_TILE = 128 * 8
 PACK_BIG_TILES_PER_CU = 4
@@ -97,7 +98,7 @@ def reduce_form(waves_per_cu, world_size, off_grid, off_lines):
     """The reduce's template numbers: sources in flight, resident waves,
     off-grid form, tiles in runs (`off_lines`: most of them are off the lines)."""
     batch = 1 if waves_per_cu >= REDUCE_ONE_WAVES else 2 if waves_per_cu >= REDUCE_TWO_WAVES else 4
-    large = waves_per_cu >= REDUCE_CAP_WAVES
+    large = waves_per_cu >= (REDUCE_SOME_WAVES if world_size <= REDUCE_SOME_W else REDUCE_CAP_WAVES)
     wide = world_size >= REDUCE_WIDE_W and waves_per_cu >= REDUCE_WIDE_WAVES
 
     def flag(x):
@@ -106,8 +107,10 @@ def reduce_form(waves_per_cu, world_size, off_grid, off_lines):
     if off_grid:
         return (4, 8, "true", "false") if batch == 4 else (2, 4, "true", flag(off_lines))
     if large:
-        runs = off_lines or not (wide and waves_per_cu >= REDUCE_PLAIN_WAVES)
-        return (1, 3 if wide else 8 if world_size <= REDUCE_FEW_W else 4, "false", flag(runs))
+        rounds = (waves_per_cu < REDUCE_PLAIN_WAVES if world_size < REDUCE_WIDE_W
+                  else wide and waves_per_cu < REDUCE_WIDE_PLAIN_WAVES)
+        uncapped = world_size <= (REDUCE_FEW_W if rounds else REDUCE_FEWEST_W)
+        return (1, 3 if wide else 8 if uncapped else 4, "false", flag(off_lines or rounds))
     return (batch, 8, "false", flag(off_lines and batch < 4))
 
 

@@ -76,10 +76,14 @@ static_assert(kCopyBlock % 64 == 0 && kWidenBlock % 64 == 0 && kPackBlock % 64 =
               "workgroups are whole wavefronts, the reduction's one wavefront");
 constexpr int kReduceWaves = FSDP_REDUCE_WAVES;           // resident waves per SIMD of a large shard's reduction
 constexpr int kReduceCapWaves = FSDP_REDUCE_CAP_WAVES;    // waves per CU from which a shard is large
-constexpr int kReduceFewW = 7;                            // ... and W up to which none is capped
-constexpr int kReduceWideW = 32;                          // ... and W from which one wave fewer is resident,
+constexpr int kReduceSomeW = 11;                          // ... and W up to which it is large
+constexpr int kReduceSomeWaves = 32;                      // ... from here only;
+constexpr int kReducePlainWaves = 192;                    // ... tiles on the lines are in plain order from here
+constexpr int kReduceFewestW = 3;                         // ... W up to which no shard is capped
+constexpr int kReduceFewW = 7;                            // ... and W up to which none whose tiles are in runs is
+constexpr int kReduceWideW = 32;                          // ... W from which one wave fewer is resident
 constexpr int kReduceWideWaves = 32;                      // ... in a shard of as many waves per CU,
-constexpr int kReducePlainWaves = 96;                     // ... and tiles on the lines are in plain order from here
+constexpr int kReduceWidePlainWaves = 96;                 // ... which is in plain order from here
 constexpr int kReduceOneWaves = FSDP_REDUCE_ONE_WAVES;    // ... from which a wave keeps one source in flight, not two
 constexpr int kReduceTwoWaves = FSDP_REDUCE_TWO_WAVES;    // ... two sources, not four
 constexpr int kReduceThroughW = 4;                        // W up to which an fp32 wire's averages always write through
@@ -1679,9 +1683,13 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     // W = 48: 404 / 416 / 436; 8B block, W = 8: 88 / 87 / 89; five segments on
     // the lines, W = 16, 31 waves per CU: 26.5 / 24.8 / 26.8, 64 waves: 49.5 / 46.3
     // / 49.5.  A wave of few sources is not long in its stream, and needs the
-    // others beside it: W = 3, 64 waves per CU 19.8 / 18.1 / 16.8.
+    // others beside it, with more sources unless the shard takes many rounds: W = 3,
+    // 64 waves per CU 19.8 / 18.1 / 16.8; 4 / 8: W = 1, 200 waves 31.0 / 27.3, W = 4, fp32,
+    // 600 waves 119 / 125, W = 8, fp16, 28 waves 15.1 / 14.4, W = 64, fp32, 28 waves 68.9 /
+    // 73.8.
     const auto from = [&](int per_cu) { return waves >= int64_t(per_cu) * cus; };
-    bool large = from(kReduceCapWaves), wide = pl.world >= kReduceWideW && from(kReduceWideWaves);
+    bool large = from(pl.world <= kReduceSomeW ? kReduceSomeWaves : kReduceCapWaves);
+    bool wide = pl.world >= kReduceWideW && from(kReduceWideWaves);
     int batch = from(kReduceOneWaves) ? 1 : from(kReduceTwoWaves) ? 2 : 4;
     if (pl.reduce_tiles == FSDP_REDUCE_TILES_FULL) large = true, wide = pl.world >= kReduceWideW, batch = 1;
     if (pl.reduce_tiles == FSDP_REDUCE_TILES_HALF) large = wide = false, batch = 4;
@@ -1694,12 +1702,15 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
     // has no such order: 8 runs are 8 waves per CU.)
     //
     // On the lines runs are better where a shard takes a few rounds of resident
-    // waves (W = 64, 40 waves per CU: 117 / 107; W = 8, 36 waves: 19.6 / 18.4)
-    // and, of fewer sources, beyond (70B block's TP-8 shards, W = 8: 45.6 / 44.3),
-    // no better where all of it is resident (8B block, W = 128: 63.4 / 64.8) or W
-    // is large and the shard too (70B block 262 / 264, uneven bucket 400 / 408).
+    // waves, plain / runs: W = 64, 32 waves per CU 87.9 / 83.5 us, 40 waves 117 / 107; W
+    // = 16, 96 waves 73.7 / 71.3, 128 waves 97.4 / 94.4; 70B block's TP-8 shards, W = 8:
+    // 45.6 / 44.4.  They are no better where most of it is resident (W = 128, fp32,
+    // 30 waves: 146 / 153; 8B block, fp32: 129 / 131) or where it takes many rounds
+    // (W = 16, 300 waves: 220 / 226, 600 waves: 437 / 460; 8B block, W = 8, fp32: 150 /
+    // 153; 70B block, W = 64: 262 / 264).
     const bool off = 2 * waves_off > waves;
-    const bool runs = off || (large && !(wide && from(kReducePlainWaves)));
+    const bool rounds = pl.world >= kReduceWideW ? wide && !from(kReduceWidePlainWaves) : large && !from(kReducePlainWaves);
+    const bool runs = off || rounds;
     // Tiles of the parameters with the fewest tiles are numbered (and so
     // dispatched) first: a ragged last tile sums its W sources in a longer
     // dependent chain, which then overlaps the bulk instead of trailing it.
@@ -1731,7 +1742,8 @@ fsdp_status do_rs_reduce(const Plan& pl, int32_t rank, const Chunks& src, const 
         return launch_reduce<Chunks, T, 2, kReduceWaves, true, false>(pl, a, stream);
     }
     if (wide) return launch_reduce<Chunks, T, 1, kReduceWaves - 1>(pl, a, runs, stream);
-    if (large && pl.world > kReduceFewW) return launch_reduce<Chunks, T, 1, kReduceWaves, false, true>(pl, a, stream);
+    if (large && pl.world > (rounds ? kReduceFewW : kReduceFewestW))
+        return launch_reduce<Chunks, T, 1, kReduceWaves>(pl, a, runs, stream);
     if (batch == 1) return launch_reduce<Chunks, T, 1, 8>(pl, a, runs, stream);
     if (batch == 2) return launch_reduce<Chunks, T, 2, 8>(pl, a, runs, stream);
     return launch_reduce<Chunks, T, 4, 8, false, false>(pl, a, stream);

@@ -172,7 +172,7 @@ def test_reduce_forms(w, waves_per_cu, align):
 
 
 @pytest.mark.parametrize("off", [0, 8])
-@pytest.mark.parametrize("w,waves_per_cu", [(2, 5), (5, 10), (9, 26), (9, 32), (33, 32)])
+@pytest.mark.parametrize("w,waves_per_cu", [(2, 5), (5, 10), (9, 26), (9, 32), (12, 26), (33, 28), (33, 32)])
 def test_reduce_tile_order(w, waves_per_cu, off):
     """One bucket buffer whose segments and chunks lie on the 128-byte lines,
     and 16 bytes off them (where the tiles are dealt to the dies in runs): the

@@ -81,13 +81,19 @@ def test_forced_reduce_form(launches, tiles, world, form):
 
 
 @pytest.mark.parametrize("world,forms", [
-    (1, {4: "4, 8, false", 5: "2, 8, false", 10: "1, 8, false", 25: "1, 8, false", 26: "1, 8, true",
-         200: "1, 8, true"}),
-    (7, {9: "2, 8, false", 10: "1, 8, false", 25: "1, 8, false", 26: "1, 8, true", 200: "1, 8, true"}),
-    (8, {9: "2, 8, false", 10: "1, 8, false", 25: "1, 8, false", 26: "1, 4, true", 200: "1, 4, true"}),
-    (31, {25: "1, 8, false", 26: "1, 4, true", 200: "1, 4, true"}),
-    (32, {25: "1, 8, false", 26: "1, 4, true", 31: "1, 4, true", 32: "1, 3, true", 95: "1, 3, true", 96: "1, 3, false"}),
-    (128, {31: "1, 4, true", 32: "1, 3, true", 96: "1, 3, false", 200: "1, 3, false"}),
+    (1, {4: "4, 8, false", 5: "2, 8, false", 10: "1, 8, false", 31: "1, 8, false", 32: "1, 8, true",
+         191: "1, 8, true", 192: "1, 8, false"}),
+    (3, {192: "1, 8, false"}),
+    (4, {191: "1, 8, true", 192: "1, 4, false"}),
+    (7, {9: "2, 8, false", 10: "1, 8, false", 31: "1, 8, false", 32: "1, 8, true", 191: "1, 8, true",
+         192: "1, 4, false"}),
+    (8, {9: "2, 8, false", 10: "1, 8, false", 31: "1, 8, false", 32: "1, 4, true", 191: "1, 4, true",
+         192: "1, 4, false"}),
+    (11, {31: "1, 8, false", 32: "1, 4, true"}),
+    (12, {25: "1, 8, false", 26: "1, 4, true", 191: "1, 4, true", 192: "1, 4, false"}),
+    (31, {25: "1, 8, false", 26: "1, 4, true", 191: "1, 4, true", 192: "1, 4, false"}),
+    (32, {25: "1, 8, false", 26: "1, 4, false", 31: "1, 4, false", 32: "1, 3, true", 95: "1, 3, true", 96: "1, 3, false"}),
+    (128, {26: "1, 4, false", 31: "1, 4, false", 32: "1, 3, true", 96: "1, 3, false", 200: "1, 3, false"}),
 ])
 def test_reduce_form_by_size(launches, world, forms):
     """Resident waves and tile order of a shard on the lines, on both sides of
@@ -165,7 +171,7 @@ def every_form():
     calls += [{"call": c, "world": 4, "dims": small, **off}
               for c in ("ag_pack", "ag_unpack", "rs_pack") for off in ({}, odd)]
     reduces = [("rs_reduce", "bf16"), ("rs_reduce_ex", "bf16"), ("rs_reduce_ex", "f16"), ("rs_reduce_ex", "f32")]
-    for world, waves, (call, wire) in itertools.product((2, 8, 40), (1, 7, 20, 40, 70, 100), reduces):
+    for world, waves, (call, wire) in itertools.product((2, 8, 40), (1, 7, 20, 28, 40, 70, 100), reduces):
         dims = shard_of(world, waves * CUS, 256 if wire == "f32" else 512)
         calls += [{"call": call, "world": world, "wire": wire, "dims": d, "align": align}
                   for d, align in ((dims, 8), ([[8 * world, 1], *dims], 8), ([[9, 1], *dims], 1))]

@@ -38,7 +38,8 @@
  *     error nothing is enqueued and no output is touched.
  *   - Bucket buffers (send_chunk, gathered, send_buf, recv) must be 16-byte
  *     aligned.  Per-parameter pointers need only element alignment (4 bytes
- *     for fp32, 2 for bf16); unaligned ones take a slower element-wise path.
+ *     for fp32, 2 for bf16); off the 16-byte grid the kernels' any-address
+ *     forms take them, at nearly the same rate.
  *     A per-parameter pointer may be NULL only when it has no elements.
  *   - Outputs must not overlap inputs or each other (checked on the host).
  *   - A plan is needed only while a call runs: the kernel arguments are
